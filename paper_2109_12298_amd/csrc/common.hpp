@@ -90,6 +90,15 @@ __device__ __forceinline__ i64 xcd_swizzle(i64 b, i64 nb)
     return x * q + (x < r ? x : r) + k;
 }
 
+// the same in 32 bits (a 64-bit division by a run-time value costs a wave
+// over a hundred scalar instructions, before its first load)
+__device__ __forceinline__ uint32_t xcd_swizzle32(uint32_t b, uint32_t nb)
+{
+    const uint32_t q = nb / kXcds, r = nb % kXcds;
+    const uint32_t x = b % kXcds, k = b / kXcds;
+    return x * q + (x < r ? x : r) + k;
+}
+
 // ---------------------------------------------------------------------------
 // device-side status flags (rare: only on bad input)
 // ---------------------------------------------------------------------------

@@ -15,7 +15,7 @@
 #include "conv2d_small_dev.hpp"
 #include "grad_sample_bf16.hpp"
 #include "linear_outer.hpp"
-#include "linear_staged.hpp"
+#include "ps_split.hpp"
 
 namespace dpg {
 namespace {
@@ -114,8 +114,8 @@ bool staged(const dp_layer_grad &L, dp_dtype dt, i64 N)
            bf16_staged_ok(L.A, L.B, L.gW, N, L.T, L.d_in, L.d_out);
 }
 
-// an fp32 Linear layer over a sequence that the staged fp32 kernel takes:
-// these layers share a launch of their own (fp32_grad_sample_group)
+// an fp32 Linear layer over a sequence that goes into the launch
+// that these layers share (ps_split_group)
 bool staged32(const dp_layer_grad &L, dp_dtype dt, i64 N)
 {
     return validate(L, dt, N) == DP_OK && N > 0 && L.kind == DP_LAYER_LINEAR && dt == DP_F32 && L.T > 1 &&
@@ -143,7 +143,7 @@ size_t staged_partials_bytes(const dp_layer_grad &L, i64 N)
 
 size_t staged32_partials_bytes(const dp_layer_grad &L, i64 N)
 {
-    return L.sqnorm ? align_up((size_t)N * fp32_staged_parts(L.d_in, L.d_out) * sizeof(float), 256) : 0;
+    return L.sqnorm ? align_up((size_t)N * ps_split_parts(L.d_in, L.d_out) * sizeof(float), 256) : 0;
 }
 
 size_t single_workspace(const dp_layer_grad &L, dp_dtype dt, i64 N)
@@ -304,14 +304,14 @@ extern "C" dp_status dp_grad_sample_many(const dp_layer_grad *items, int32_t cou
         if (st != DP_OK) return st;
     }
 
-    // fp32 sequence layers on the staged kernel, in launches of up to
+    // fp32 sequence layers, in launches of up to
     // kPsGroupMax, their norm partials one layer after another in the scratch
     {
-        Fp32GroupLayer grp[kPsGroupMax];
+        PsLayer grp[kPsGroupMax];
         int n = 0;
         size_t off = 0;
         auto flush = [&]() {
-            fp32_grad_sample_group(grp, n, N, stream);
+            ps_split_group(grp, n, N, stream);
             n = 0;
             off = 0;
         };
@@ -319,7 +319,7 @@ extern "C" dp_status dp_grad_sample_many(const dp_layer_grad *items, int32_t cou
             const dp_layer_grad &L = items[k];
             if (!staged32(L, dt, N)) continue;
             if (n == kPsGroupMax) flush();
-            grp[n++] = Fp32GroupLayer{L.A, L.B, L.T, L.d_in, L.d_out, L.scale, L.gW, L.gb, L.sqnorm,
+            grp[n++] = PsLayer{L.A, L.B, L.T, L.d_in, L.d_out, L.scale, L.gW, L.gb, L.sqnorm,
                                       L.sqnorm ? (float *)((char *)ws + off) : nullptr};
             off += staged32_partials_bytes(L, N);
         }

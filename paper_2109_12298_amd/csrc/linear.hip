@@ -15,31 +15,13 @@
 #include "linear_bf16.hpp"
 #include "grad_sample_bf16.hpp"
 #include "linear_outer.hpp"
-#include "bf16_stage.hpp"
-#include "linear_staged.hpp"
+#include "ps_split.hpp"
 
 namespace dpg {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kBM = 64, kBN = 64, kBK = 32;
-
-template <typename T>
-__device__ __forceinline__ float4 load4(const T *p, i64 i);
-
-template <>
-__device__ __forceinline__ float4 load4<float>(const float *p, i64 i)
-{
-    return *reinterpret_cast<const float4 *>(p + i);
-}
-
-template <>
-__device__ __forceinline__ float4 load4<uint16_t>(const uint16_t *p, i64 i)
-{
-    const uint2 u = *reinterpret_cast<const uint2 *>(p + i);
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                       __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-}
 
 // T = 1: the rank-one outer product (linear_outer.hpp), block = (sample, rows)
 template <typename T, bool VEC>
@@ -54,27 +36,16 @@ __global__ __launch_bounds__(kThreads) void outer_kernel(const T *__restrict__ A
 
 // ---------------------------------------------------------------------------
 // T > 1: per-sample GEMM on MFMA.  Block = (sample n, 64 x 64 tile of gW_n).
-// MFMA rows run over j (d_in, the contiguous index of gW), so each lane ends
-// with four consecutive entries of a row of gW and stores them as one float4;
-// columns run over i (d_out).  Both operands are staged K-major exactly as
-// they lie in memory ([t][feature]), with 16-byte loads when the rows allow;
-// the next chunk of positions is loaded into registers while the current
-// one is multiplied.
+// The kernel of layers whose rows are shorter than the 16-byte loads of
+// ps_split.hip (fewer than four fp32 or eight bf16 features on a side): element loads,
+// fp32 MFMA.  MFMA rows run over j (d_in, the contiguous index of gW),
+// columns over i (d_out).  Both operands are staged K-major exactly as they
+// lie in memory ([t][feature]); the next chunk of positions is loaded into
+// registers while the current one is multiplied.
 // ---------------------------------------------------------------------------
 constexpr int kPM = 64, kPN = 64, kPK = 32;
 
-template <typename T, int VEC>
-__device__ __forceinline__ void load_group(const T *p, float (&v)[VEC])
-{
-    if constexpr (VEC == 4) {
-        const float4 q = load4<T>(p, 0);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    } else {
-        v[0] = load_elem<T>(p, 0);
-    }
-}
-
-template <typename T, int VEC>
+template <typename T>
 __global__ __launch_bounds__(kThreads) void ps_gemm_kernel(
     const T *__restrict__ A, const T *__restrict__ B, i64 Tn, i64 din, i64 dout, int tiles_j,
     int tiles, float scale, float *__restrict__ gW, float *__restrict__ gb,
@@ -94,40 +65,26 @@ __global__ __launch_bounds__(kThreads) void ps_gemm_kernel(
     const T *Bn = B + n * Tn * dout;
     const bool do_bias = gb != nullptr && tj == 0;
 
-    // staging: VEC-wide groups, group g = tid + 256 q at row g / GPR
-    constexpr int GPR = kPM / VEC;
-    constexpr int NG = kPK * kPM / VEC / kThreads;
-    static_assert(kPM == kPN && NG * VEC * kThreads == kPK * kPM, "staging map");
-    float ra[NG][VEC], rb[NG][VEC];
+    constexpr int NG = kPK * kPM / kThreads;
+    static_assert(kPM == kPN && NG * kThreads == kPK * kPM, "staging map");
+    float ra[NG], rb[NG];
     auto load = [&](i64 t0) {
 #pragma unroll
         for (int q = 0; q < NG; ++q) {
             const int g = tid + kThreads * q;
-            const int r = g / GPR, c = (g % GPR) * VEC;
+            const int r = g / kPM, c = g % kPM;
             const i64 t = t0 + r;
-            const bool okA = t < Tn && j0 + c < din;   // VEC = 4: d_in % 4 == 0, whole group in or out
+            const bool okA = t < Tn && j0 + c < din;
             const bool okB = t < Tn && i0 + c < dout;
-            load_group<T, VEC>(An + (okA ? t * din + j0 + c : 0), ra[q]);
-            load_group<T, VEC>(Bn + (okB ? t * dout + i0 + c : 0), rb[q]);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                ra[q][v] = okA ? ra[q][v] : 0.0f;
-                rb[q][v] = okB ? rb[q][v] : 0.0f;
-            }
+            ra[q] = okA ? load_elem<T>(An, t * din + j0 + c) : 0.0f;
+            rb[q] = okB ? load_elem<T>(Bn, t * dout + i0 + c) : 0.0f;
         }
     };
     auto store = [&]() {
 #pragma unroll
         for (int q = 0; q < NG; ++q) {
-            const int g = tid + kThreads * q;
-            const int r = g / GPR, c = (g % GPR) * VEC;
-            if constexpr (VEC == 4) {
-                *reinterpret_cast<float4 *>(As + r * kPM + c) = make_float4(ra[q][0], ra[q][1], ra[q][2], ra[q][3]);
-                *reinterpret_cast<float4 *>(Bs + r * kPN + c) = make_float4(rb[q][0], rb[q][1], rb[q][2], rb[q][3]);
-            } else {
-                As[r * kPM + c] = ra[q][0];
-                Bs[r * kPN + c] = rb[q][0];
-            }
+            As[tid + kThreads * q] = ra[q];
+            Bs[tid + kThreads * q] = rb[q];
         }
     };
 
@@ -164,17 +121,10 @@ __global__ __launch_bounds__(kThreads) void ps_gemm_kernel(
             const i64 j = j0 + wm + 8 * rb4 + 4 * (lane >> 5);
             const float g0 = scale * acc[4 * rb4 + 0], g1 = scale * acc[4 * rb4 + 1];
             const float g2 = scale * acc[4 * rb4 + 2], g3 = scale * acc[4 * rb4 + 3];
-            if (VEC == 4) {
-                if (j < din) {
-                    *reinterpret_cast<float4 *>(G + j) = make_float4(g0, g1, g2, g3);
-                    sq += g0 * g0 + g1 * g1 + g2 * g2 + g3 * g3;
-                }
-            } else {
-                if (j + 0 < din) { G[j + 0] = g0; sq += g0 * g0; }
-                if (j + 1 < din) { G[j + 1] = g1; sq += g1 * g1; }
-                if (j + 2 < din) { G[j + 2] = g2; sq += g2 * g2; }
-                if (j + 3 < din) { G[j + 3] = g3; sq += g3 * g3; }
-            }
+            if (j + 0 < din) { G[j + 0] = g0; sq += g0 * g0; }
+            if (j + 1 < din) { G[j + 1] = g1; sq += g1 * g1; }
+            if (j + 2 < din) { G[j + 2] = g2; sq += g2 * g2; }
+            if (j + 3 < din) { G[j + 3] = g3; sq += g3 * g3; }
         }
     }
     if (do_bias && tid < kPN && i0 + tid < dout) {
@@ -186,245 +136,10 @@ __global__ __launch_bounds__(kThreads) void ps_gemm_kernel(
     if (partial && tid == 0) partial[n * tiles + tile] = sq;
 }
 
-// ---------------------------------------------------------------------------
-// T > 1, fp32, staged straight into LDS (T % 16 == 0, d_in and d_out
-// multiples of 4, 16-byte aligned operands).  Block = (sample n, 64 x 64
-// tile of gW_n) as above.  Stages of 16 positions of both tiles (4 KB each)
-// are copied by global_load_lds_dwordx4 into a ring of four, and the waves
-// wait for exactly the stage they need: no operand passes through registers
-// on its way to LDS, so no wait for a later stage's loads couples in.  A
-// stage's operands are read into registers one stage ahead, while the
-// previous stage's MFMAs run.  Inside a row the 16-byte chunks of
-// odd rows are shifted by half a row, so the two rows a wave's operand read
-// touches fall in different banks.  Each wave keeps two accumulators (odd
-// and even k-steps: two independent MFMA chains), added at the end; the bias
-// gradient is the column sum of the B operands the waves already hold.  Features past the layer's edge read a clamped valid chunk, whose
-// outputs are never stored.
-// ---------------------------------------------------------------------------
-constexpr int kDK = 16;                          // positions per stage
-constexpr int kDStages = 4;
-constexpr int kDRow = kPM * 4;                   // bytes per staged row (64 floats)
-constexpr int kDTile = kDK * kDRow;              // 4 KB per operand tile and stage
-constexpr int kDStageBytes = 2 * kDTile;
-
-__device__ __forceinline__ int dma_chunk_pos(int row, int chunk) { return chunk ^ (8 * (row & 1)); }
-
-// LDS of one workgroup of the staged kernels
-struct DmaShared {
-    __attribute__((aligned(1024))) char ring[kDStages * kDStageBytes];
-    float red[16];
-    float bred[2][kPN];
-};
-
-// Tile `tile` of sample n (the body of the single-layer and grouped launches)
-__device__ __forceinline__ void ps_dma_tile(const float *__restrict__ A, const float *__restrict__ B, i64 Tn,
-                                            i64 din, i64 dout, int tiles_j, int tiles, i64 n, int tile,
-                                            float scale, float *__restrict__ gW, float *__restrict__ gb,
-                                            float *__restrict__ partial, DmaShared &sh)
+// the fp32 layers that dp_grad_sample_many groups into one launch
+bool grouped_shape_ok(const void *A, const void *B, const float *gW, i64 T, i64 din, i64 dout)
 {
-    char *smem = sh.ring;
-    float *red = sh.red;
-    float (*bred)[kPN] = sh.bred;
-    const int ti = tile / tiles_j, tj = tile % tiles_j;
-    const i64 j0 = (i64)tj * kPM, i0 = (i64)ti * kPN;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-    const bool do_bias = gb != nullptr && tj == 0;
-    const int nst = (int)(Tn / kDK);
-    const uint32_t lds0 = bf16s::lds_addr(smem);
-
-    // wave w copies rows 4w .. 4w+3 of both tiles of a stage (one 1 KB
-    // instruction each): lane l -> row 4w + l / 16, LDS chunk l % 16, which
-    // holds feature chunk dma_chunk_pos(row, l % 16) of that row
-    const int srow = 4 * wave + lane / 16;
-    const int schunk = dma_chunk_pos(srow, lane % 16);
-    i64 fa = j0 + 4 * schunk, fb = i0 + 4 * schunk;
-    fa = fa < din ? fa : din - 4;
-    fb = fb < dout ? fb : dout - 4;
-    const float *An = A + n * Tn * din + (i64)srow * din + fa;
-    const float *Bn = B + n * Tn * dout + (i64)srow * dout + fb;
-    const uint32_t lds_a = (uint32_t)(4 * wave * kDRow), lds_b = (uint32_t)(kDTile + 4 * wave * kDRow);
-    auto issue = [&](int c) {
-        const uint32_t L = lds0 + (uint32_t)(c % kDStages) * kDStageBytes;
-        bf16s::dma16(An + (i64)c * kDK * din, L + lds_a);
-        bf16s::dma16(Bn + (i64)c * kDK * dout, L + lds_b);
-    };
-    constexpr int LOADS = 2;                     // per wave per stage
-
-    f32x16 acc0, acc1;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.0f;
-    // column sums of the wave's B operands: lane l holds rows of parity l / 32
-    // of column wn + l % 32 (the bias gradient, from the registers the MFMAs read)
-    float bias_acc = 0.0f;
-    const int li = lane & 31, lk = lane >> 5;
-    // operand addresses inside a stage: A feature wm + li, B feature wn + li, row kk + lk
-    auto opnd = [&](int row, int f) { return row * kDRow + 16 * dma_chunk_pos(row, f >> 2) + 4 * (f & 3); };
-
-    // a stage's operands in registers: k-steps 0, 2, .., 14 of the wave's A and B columns
-    struct Ops {
-        float a[kDK / 2], b[kDK / 2];
-    };
-    auto read_ops = [&](int c, Ops &o) {
-        const char *L = smem + (c % kDStages) * kDStageBytes;
-#pragma unroll
-        for (int k = 0; k < kDK / 2; ++k) {
-            o.a[k] = *reinterpret_cast<const float *>(L + opnd(2 * k + lk, wm + li));
-            o.b[k] = *reinterpret_cast<const float *>(L + kDTile + opnd(2 * k + lk, wn + li));
-        }
-    };
-    auto mma = [&](const Ops &o) {
-#pragma unroll
-        for (int k = 0; k < kDK / 2; k += 2) {
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[k], o.b[k], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[k + 1], o.b[k + 1], acc1, 0, 0, 0);
-        }
-        float s = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kDK / 2; ++k) s += o.b[k];
-        bias_acc += s;
-    };
-    // stage c has landed once only the loads of the `later` stages after it remain
-    auto wait_landed = [&](int later) {
-        if (later >= 3) bf16s::wait_vmcnt<3 * LOADS>();
-        else if (later == 2) bf16s::wait_vmcnt<2 * LOADS>();
-        else if (later == 1) bf16s::wait_vmcnt<LOADS>();
-        else bf16s::wait_vmcnt<0>();
-    };
-
-    // Per stage c (its operands already in registers): wait for stage c+1,
-    // meet at the barrier (every wave has its stage c operands, so stage c's
-    // buffer may take stage c+4), issue stage c+4, then the MFMAs of stage c
-    // with the reads of stage c+1 between them.
-#pragma unroll
-    for (int c = 0; c < kDStages; ++c)
-        if (c < nst) issue(c);
-    // one stage c < nst - 1: its MFMAs (operands in cur) and the reads of stage c+1 into nxt
-    auto step = [&](int c, const Ops &cur, Ops &nxt) {
-        wait_landed(nst - 2 - c < kDStages - 2 ? nst - 2 - c : kDStages - 2);
-        bf16s::wait_lgkmcnt0();
-        bf16s::stage_barrier();
-        if (c + kDStages < nst) issue(c + kDStages);
-        read_ops(c + 1, nxt);
-        mma(cur);
-#pragma unroll
-        for (int k = 0; k < kDK / 2; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read (two rows)
-        }
-    };
-    Ops x, y;   // two register sets, stages alternate between them
-    if (nst > 0) {
-        wait_landed(nst - 1 < kDStages - 1 ? nst - 1 : kDStages - 1);
-        bf16s::stage_barrier();
-        read_ops(0, x);
-        int c = 0;
-        for (; c + 2 < nst; c += 2) {
-            step(c, x, y);
-            step(c + 1, y, x);
-        }
-        if (c + 1 < nst) {   // two stages left
-            step(c, x, y);
-            x = y;
-        }
-        mma(x);
-    }
-
-    // acc[r] holds gW[i][j], j = j0 + wm + 8 (r / 4) + 4 (lane / 32) + r % 4, i = i0 + wn + lane % 32
-    float sq = 0.0f;
-    const i64 i = i0 + wn + (lane & 31);
-    if (i < dout) {
-        float *G = gW + n * dout * din + i * din;
-#pragma unroll
-        for (int rb4 = 0; rb4 < 4; ++rb4) {
-            const i64 j = j0 + wm + 8 * rb4 + 4 * (lane >> 5);
-            const float g0 = scale * (acc0[4 * rb4 + 0] + acc1[4 * rb4 + 0]);
-            const float g1 = scale * (acc0[4 * rb4 + 1] + acc1[4 * rb4 + 1]);
-            const float g2 = scale * (acc0[4 * rb4 + 2] + acc1[4 * rb4 + 2]);
-            const float g3 = scale * (acc0[4 * rb4 + 3] + acc1[4 * rb4 + 3]);
-            if (j < din) {   // d_in % 4 == 0: the four j are all in or all out
-                *reinterpret_cast<float4 *>(G + j) = make_float4(g0, g1, g2, g3);
-                sq += g0 * g0 + g1 * g1 + g2 * g2 + g3 * g3;
-            }
-        }
-    }
-    if (do_bias) {
-        // waves 0 and 2 (wm == 0) hold columns 0..31 and 32..63; a column's
-        // even rows (lane l) and odd rows (lane l + 32) are added in that order
-        if (wm == 0 && lane < 32) bred[0][wn + lane] = bias_acc;
-        if (wm == 0 && lane >= 32) bred[1][wn + lane - 32] = bias_acc;
-        __syncthreads();
-        if (tid < kPN && i0 + tid < dout) {
-            const float g = scale * (bred[0][tid] + bred[1][tid]);
-            gb[n * dout + i0 + tid] = g;
-            sq += g * g;
-        }
-    }
-    sq = block_sum(sq, red);
-    if (partial && tid == 0) partial[n * tiles + tile] = sq;
-}
-
-__global__ __launch_bounds__(kThreads) void ps_gemm_dma_kernel(const float *__restrict__ A, const float *__restrict__ B,
-                                                               i64 Tn, i64 din, i64 dout, int tiles_j, int tiles,
-                                                               float scale, float *__restrict__ gW,
-                                                               float *__restrict__ gb, float *__restrict__ partial)
-{
-    __shared__ DmaShared sh;
-    const i64 bsw = xcd_swizzle(blockIdx.x, gridDim.x);
-    ps_dma_tile(A, B, Tn, din, dout, tiles_j, tiles, bsw / tiles, (int)(bsw % tiles), scale, gW, gb, partial, sh);
-}
-
-// Several staged layers sharing N in one launch: workgroup b takes sample
-// b / tiles_all and, of that sample's tiles of all layers (layer after layer),
-// tile b % tiles_all, so layers that read the same B (an LSTM's two weight
-// matrices) read it while it is in L2.
-struct PsDmaItem {
-    const float *A, *B;
-    i64 T, din, dout;
-    int tiles_j, tiles, tile0;
-    float scale;
-    float *gW, *gb, *sqnorm, *partial;
-};
-struct PsDmaGroup {
-    int count, tiles_all;
-    i64 N;
-    PsDmaItem it[kPsGroupMax];
-};
-
-__global__ __launch_bounds__(kThreads) void ps_dma_group_kernel(const PsDmaGroup g)
-{
-    __shared__ DmaShared sh;
-    const i64 bsw = xcd_swizzle(blockIdx.x, gridDim.x);
-    const i64 n = bsw / g.tiles_all;
-    const int r = (int)(bsw % g.tiles_all);
-    int k = 0;
-    while (k + 1 < g.count && g.it[k + 1].tile0 <= r) ++k;
-    const PsDmaItem &L = g.it[k];
-    ps_dma_tile(L.A, L.B, L.T, L.din, L.dout, L.tiles_j, L.tiles, n, r - L.tile0, L.scale, L.gW, L.gb, L.partial,
-                sh);
-}
-
-// One wave per (layer, sample): sqnorm[n] = the sample's tile partials added
-// as sum_partials adds them (lane l takes partials l, l+64, ..., then the
-// same butterfly), so the grouped launch matches the single-layer call bit
-// for bit.
-__global__ __launch_bounds__(256) void ps_dma_group_sqnorm_kernel(const PsDmaGroup g)
-{
-    const PsDmaItem &L = g.it[blockIdx.y];
-    const i64 n = (i64)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (L.sqnorm == nullptr || n >= g.N) return;
-    const float *p = L.partial + n * L.tiles;
-    float s = 0.0f;
-    for (int t = lane; t < L.tiles; t += kWave) s += p[t];
-    s = wave_sum(s);
-    if (lane == 0) L.sqnorm[n] = s;
-}
-
-bool ps_dma_ok(const void *A, const void *B, const float *gW, i64 T, i64 din, i64 dout)
-{
-    return T >= kDK && T % kDK == 0 && din % 4 == 0 && dout % 4 == 0 && aligned(A, 16) && aligned(B, 16) &&
+    return T >= 16 && T % 16 == 0 && din % 4 == 0 && dout % 4 == 0 && aligned(A, 16) && aligned(B, 16) &&
            aligned(gW, 16) && T * (din > dout ? din : dout) < (i64(1) << 31);
 }
 
@@ -526,47 +241,8 @@ ClipSplit clip_split(i64 N, i64 T, i64 din, i64 dout)
 
 bool fp32_staged_ok(const void *A, const void *B, const void *gW, i64 N, i64 T, i64 din, i64 dout)
 {
-    return ps_dma_ok(A, B, (const float *)gW, T, din, dout) && N < (i64(1) << 40) &&
-           N * ceil_div(din, kPM) * ceil_div(dout, kPN) < (i64(1) << 26);
-}
-
-int fp32_staged_parts(i64 din, i64 dout) { return (int)(ceil_div(din, kPM) * ceil_div(dout, kPN)); }
-
-void fp32_grad_sample_group(const Fp32GroupLayer *layers, int count, i64 N, hipStream_t stream)
-{
-    if (count <= 0 || N <= 0) return;
-    PsDmaGroup g;
-    g.count = count;
-    g.N = N;
-    int tiles_all = 0;
-    bool norms = false;
-    for (int k = 0; k < count; ++k) {
-        const Fp32GroupLayer &L = layers[k];
-        PsDmaItem &it = g.it[k];
-        it.A = (const float *)L.A;
-        it.B = (const float *)L.B;
-        it.T = L.T;
-        it.din = L.din;
-        it.dout = L.dout;
-        it.tiles_j = (int)ceil_div(L.din, kPM);
-        it.tiles = fp32_staged_parts(L.din, L.dout);
-        it.tile0 = tiles_all;
-        it.scale = L.scale;
-        it.gW = L.gW;
-        it.gb = L.gb;
-        it.sqnorm = L.sqnorm;
-        it.partial = L.sqnorm ? L.partial : nullptr;
-        tiles_all += it.tiles;
-        norms = norms || L.sqnorm != nullptr;
-    }
-    for (int k = count; k < kPsGroupMax; ++k) {
-        g.it[k] = g.it[count - 1];
-        g.it[k].tile0 = tiles_all;
-    }
-    g.tiles_all = tiles_all;
-    ps_dma_group_kernel<<<(unsigned)(N * tiles_all), kThreads, 0, stream>>>(g);
-    if (norms)
-        ps_dma_group_sqnorm_kernel<<<dim3((unsigned)ceil_div(N, 4), (unsigned)count), 256, 0, stream>>>(g);
+    return grouped_shape_ok(A, B, (const float *)gW, T, din, dout) && ps_split_ok(DP_F32, T, din, dout) &&
+           N < (i64(1) << 40) && N * ceil_div(din, kPM) * ceil_div(dout, kPN) < (i64(1) << 26);
 }
 
 dp_status check_linear(const void *A, const void *B, dp_dtype dt, i64 N, i64 T, i64 din, i64 dout)
@@ -650,37 +326,20 @@ extern "C" dp_status dp_grad_sample_linear(const void *A, const void *B, dp_dtyp
             sum_partials(partial, N, bf16_tiles(d_in, d_out), sqnorm, stream);
         return launch_status();
     }
+    if (ps_split_ok(dt, T, d_in, d_out)) {
+        ps_split_grad({A, B, T, d_in, d_out, scale, gW, gb, sqnorm, partial}, dt, N, stream);
+        return launch_status();
+    }
+    // rows too short for 16-byte loads
     const int tiles_j = (int)ceil_div(d_in, kPM);
     const int tiles = (int)ceil_div(d_out, kPN) * tiles_j;
     const dim3 grid((unsigned)(N * tiles));
-    if (dt == DP_F32 && ps_dma_ok(A, B, gW, T, d_in, d_out)) {
-        ps_gemm_dma_kernel<<<grid, kThreads, 0, stream>>>((const float *)A, (const float *)B, T, d_in, d_out,
-                                                          tiles_j, tiles, scale, gW, gb, partial);
-        if (sqnorm)
-            sum_partials(partial, N, tiles, sqnorm, stream);
-        return launch_status();
-    }
-    // 16-byte (fp32) / 8-byte (bf16) operand loads and float4 stores when
-    // every row starts on such a boundary
-    const size_t ea = dt == DP_F32 ? 16 : 8;
-    const bool vec = d_in % 4 == 0 && d_out % 4 == 0 && aligned(A, ea) && aligned(B, ea) && aligned(gW, 16);
-    if (dt == DP_F32) {
-        if (vec)
-            ps_gemm_kernel<float, 4><<<grid, kThreads, 0, stream>>>(
-                (const float *)A, (const float *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb, partial);
-        else
-            ps_gemm_kernel<float, 1><<<grid, kThreads, 0, stream>>>(
-                (const float *)A, (const float *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb, partial);
-    } else {
-        if (vec)
-            ps_gemm_kernel<uint16_t, 4><<<grid, kThreads, 0, stream>>>(
-                (const uint16_t *)A, (const uint16_t *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb,
-                partial);
-        else
-            ps_gemm_kernel<uint16_t, 1><<<grid, kThreads, 0, stream>>>(
-                (const uint16_t *)A, (const uint16_t *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb,
-                partial);
-    }
+    if (dt == DP_F32)
+        ps_gemm_kernel<float><<<grid, kThreads, 0, stream>>>(
+            (const float *)A, (const float *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb, partial);
+    else
+        ps_gemm_kernel<uint16_t><<<grid, kThreads, 0, stream>>>(
+            (const uint16_t *)A, (const uint16_t *)B, T, d_in, d_out, tiles_j, tiles, scale, gW, gb, partial);
     if (sqnorm)
         sum_partials(partial, N, tiles, sqnorm, stream);
     return launch_status();
