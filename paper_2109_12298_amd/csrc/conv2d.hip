@@ -23,6 +23,7 @@
 #include "mfma_tile.hpp"
 #include "conv2d_small.hpp"
 #include "conv2d_rows.hpp"
+#include "conv2d_split.hpp"
 
 #include <type_traits>
 
@@ -656,6 +657,18 @@ int conv_path()
 }
 }  // namespace dpg
 
+// Whether the automatic choice runs the row chunks on the bf16 matrix units:
+// instead of the fp32 row-chunked kernel, and, for wide rows that that kernel's
+// stage does not hold, instead of the tiled one (64 samples, 64 -> 64 channels,
+// 56 x 56: 865 us there) where the fp32 rule says so, which then holds for both
+// types (dp_conv2d_kernel_choice does not know the type).
+static bool split_chosen(const ConvRowsArgs &rows, bool bf, int slots)
+{
+    if (g_conv_path != DP_CONV_AUTO) return false;
+    if (conv_rows_preferred(rows)) return conv_split_ok(rows, bf, slots);
+    return conv_split_ok(rows, false, slots) && conv_split_ok(rows, true, slots);
+}
+
 extern "C" int dp_conv2d_set_path(int path)
 {
     if (path != DP_CONV_AUTO && path != DP_CONV_TILED && path != DP_CONV_ROWS) return -1;
@@ -675,6 +688,8 @@ extern "C" int32_t dp_conv2d_kernel_choice(int64_t N, int64_t Cin, int64_t H, in
     const ConvRowsArgs rows{nullptr, nullptr, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw};
     if (g_conv_path == DP_CONV_ROWS ? conv_rows_ok(rows) : g_conv_path == DP_CONV_AUTO && conv_rows_preferred(rows))
         return DP_CONV_KERNEL_ROWS;
+    const size_t need = dp_grad_sample_conv2d_workspace_bytes(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw);
+    if (N > 0 && split_chosen(rows, false, need ? (int)(need / (N * sizeof(float))) : 1)) return DP_CONV_KERNEL_ROWS;
     return DP_CONV_KERNEL_TILED;
 }
 
@@ -708,6 +723,12 @@ extern "C" dp_status dp_grad_sample_conv2d(const void *X, const void *GY, dp_dty
         return launch_status();
     }
     const ConvRowsArgs rows{X, GY, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw};
+    const int slots = need ? (int)(need / (N * sizeof(float))) : 1;
+    if (split_chosen(rows, bf, slots)) {
+        // output row chunks on the bf16 matrix units
+        conv_split_launch(rows, bf, slots, scale, gW, gb, sqnorm, (float *)ws, stream);
+        return launch_status();
+    }
     if (g_conv_path == DP_CONV_ROWS ? conv_rows_ok(rows) : g_conv_path == DP_CONV_AUTO && conv_rows_preferred(rows)) {
         // output row chunks, the whole weight-column tile in registers
         conv_rows_launch(rows, bf, scale, gW, gb, sqnorm, (float *)ws, stream);

@@ -107,3 +107,89 @@ def test_linear_small_magnitudes():
     ref = np.einsum("nti,ntj->nij", B.double().numpy(), A.double().numpy())
     mag = np.einsum("nti,ntj->nij", abs(B.double().numpy()), abs(A.double().numpy()))
     assert (abs(gW - ref) <= (T + 8) * 2.0 ** -24 * mag + 2.0 ** -140).all()
+
+
+# N, Cin, Cout, H, W, k, stride, pad: the shapes the automatic choice gives the
+# bf16-matrix kernel, at the edges of its channel blocks (32, 64), units of
+# eight columns, row chunks, tap groups and shifts
+CONVS = [
+    (2, 32, 64, 16, 16, 3, 1, 1), (3, 24, 33, 15, 17, 3, 1, 1), (1, 65, 40, 13, 24, 3, 1, 0), (2, 33, 31, 20, 9, 3, 1, 2),
+    (1, 64, 64, 12, 63, 3, 1, 1), (2, 40, 130, 11, 11, 3, 1, 1), (1, 31, 64, 33, 40, 3, 2, 1), (2, 64, 64, 18, 23, 3, 2, 0),
+    (1, 24, 32, 28, 30, 3, 1, 1), (300, 32, 64, 12, 12, 3, 1, 1), (2, 25, 70, 10, 57, 3, 1, 1),
+]
+CONVS_BF16 = CONVS + [
+    (3, 24, 40, 27, 27, 5, 2, 2), (2, 40, 24, 13, 14, 5, 1, 0), (1, 24, 24, 19, 21, 7, 1, 3), (2, 26, 33, 21, 26, 4, 2, 1),
+    (1, 30, 64, 14, 15, 2, 1, 0), (2, 64, 32, 9, 9, 3, 3, 1),
+]
+
+
+def conv(X, GY, k, stride, pad, shift, scale=1.5):
+    N, ci, H, W = X.shape
+    co, ho, wo = GY.shape[1:]
+    dt = dp.dtype_of(X)
+    x, y = placed(X, shift), placed(GY, shift)
+    n = N * co * ci * k * k
+    gW = torch.full((n + shift + 64,), 7.0, device=DEV)
+    gb = torch.full((N * co + 64,), 7.0, device=DEV)
+    sq = torch.full((N,), 7.0, device=DEV)
+    geom = (k, k, stride, stride, pad, pad)
+    ws = torch.empty(max(dp.dp_grad_sample_conv2d_workspace_bytes(N, ci, H, W, co, *geom), 4), dtype=torch.uint8,
+                     device=DEV)
+    dp.dp_grad_sample_conv2d(x, y, dt, N, ci, H, W, co, ho, wo, *geom, 1, 1, 1, scale, gW[shift:], gb, sq, None, ws)
+    torch.cuda.synchronize()
+    assert (gW[:shift] == 7).all() and (gW[shift + n:] == 7).all() and (gb[N * co:] == 7).all(), "wrote outside"
+    return (gW[shift:shift + n].reshape(N, co, ci * k * k).cpu().numpy(), gb[:N * co].reshape(N, co).cpu().numpy(),
+            sq.cpu().numpy())
+
+
+def conv_reference(X, GY, k, stride, pad, scale=1.5):
+    """The gradients and the sums of the terms' magnitudes, in 64 bits."""
+    y = GY.double().flatten(2)
+    u = torch.nn.functional.unfold(X.double(), k, padding=pad, stride=stride).transpose(1, 2)
+    return scale * torch.bmm(y, u).numpy(), scale * torch.bmm(y.abs(), u.abs()).numpy(), scale * y.sum(2).numpy()
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dtype,case", [("f32", c) for c in CONVS] + [("bf16", c) for c in CONVS_BF16],
+                         ids=lambda c: c if isinstance(c, str) else "x".join(map(str, c)))
+def test_conv_edges(dtype, case, shift):
+    N, ci, co, H, W, k, st, pad = case
+    say("conv", case, dtype, "shift", shift)
+    assert dp.dp_conv2d_kernel_choice(N, ci, H, W, co, k, k, st, st, pad, pad) == dp.DP_CONV_KERNEL_ROWS
+    g = torch.Generator().manual_seed(ci * 100 + H)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ho, wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    X = torch.randn(N, ci, H, W, generator=g).to(td)
+    GY = (torch.randn(N, co, ho, wo, generator=g) / 5).to(td)
+    gW, gb, sq = conv(X, GY, k, st, pad, shift)
+    ref, mag, rb = conv_reference(X, GY, k, st, pad)
+    bound = (ho * wo + 8) * 2.0 ** -24
+    assert (abs(gW - ref) <= bound * mag).all()
+    assert (abs(gb - rb) <= bound * 1.5 * GY.double().abs().sum((2, 3)).numpy()).all()
+    sref = (gW.astype(np.float64) ** 2).sum((1, 2)) + (gb.astype(np.float64) ** 2).sum(1)
+    assert (abs(sq - sref) <= 1e-5 * sref).all()
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
+def test_conv_non_finite(value):
+    N, ci, co, H, k = 2, 40, 36, 14, 3
+    say("conv non-finite", value)
+    g = torch.Generator().manual_seed(9)
+    X, GY = torch.randn(N, ci, H, H, generator=g), torch.randn(N, co, H, H, generator=g) / 100
+    X[1, 39, 0, 13] = value                  # a corner: only some taps reach it
+    GY[1, 5] = 0.0
+    gW, gb, sq = conv(X, GY, k, 1, 1, 0, 1.0)
+    # in 64 bits the padding's zeros must not meet the value: sum tap by tap
+    Xp, ref = np.zeros((N, ci, H + 2, H + 2)), np.empty((N, co, ci, k, k))
+    Xp[:, :, 1:-1, 1:-1] = X.double().numpy()
+    with np.errstate(invalid="ignore", over="ignore"):
+        for u in range(k):
+            for v in range(k):
+                ref[:, :, :, u, v] = np.einsum("nop,ncp->noc", GY.double().numpy().reshape(N, co, -1),
+                                               Xp[:, :, u:u + H, v:v + H].reshape(N, ci, -1))
+        ref = ref.reshape(N, co, ci * k * k)
+        np.testing.assert_array_equal(np.isnan(gW), np.isnan(ref))
+        np.testing.assert_array_equal(np.isinf(gW), np.isinf(ref.astype(np.float32)))
+    ok = np.isfinite(ref)
+    assert (abs(gW[ok] - ref[ok]) <= 1e-5 * (abs(ref[ok]) + 1.0)).all() or value == 3.4e38
+    assert np.isfinite(sq[0]) and not np.isfinite(sq[1])
