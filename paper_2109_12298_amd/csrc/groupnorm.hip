@@ -7,10 +7,14 @@
 //   gbeta_n[c]  = s * sum_p B[n][c][p]
 // over the channel's P spatial positions, which are contiguous in memory.
 // A wave reduces one channel at a time (lanes over the positions, 16-byte
-// loads when the rows allow, then a fixed tree), or, for planes of at most 64
+// loads at any alignment, up to four of each operand in flight, then a fixed
+// tree), or, for planes of at most 64
 // positions, four channels at a time on 16 lanes each; the sums are
 // deterministic.  A workgroup takes 16 channels of one sample, and the
 // sample's squared norm is added over its channel blocks in block order.
+// Bound by the reads: 512 x 64 x 1024 fp32 268 MB in 45 us with the launch that adds
+// the norm's blocks (6.0 TB/s; 56 us with one pair of loads in flight), 100 x
+// 30 x 777 fp32 11 us (20 with single elements).
 #include "common.hpp"
 
 namespace dpg {
@@ -20,21 +24,15 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kChanPerBlock = 16;
 
-template <typename T>
-__device__ __forceinline__ float4 ld4(const T *p);
-
-template <>
-__device__ __forceinline__ float4 ld4<float>(const float *p)
+// Four consecutive elements at their natural alignment only; NT: past the caches.
+template <typename T, bool NT>
+__device__ __forceinline__ float4 ld4(const T *p)
 {
-    return *reinterpret_cast<const float4 *>(p);
-}
-
-template <>
-__device__ __forceinline__ float4 ld4<uint16_t>(const uint16_t *p)
-{
-    const uint2 u = *reinterpret_cast<const uint2 *>(p);
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                       __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+    typedef T v4_t __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    const v4_t *q = reinterpret_cast<const v4_t *>(p);
+    const v4_t v = NT ? __builtin_nontemporal_load(q) : *q;
+    if constexpr (sizeof(T) == 4) return make_float4(v[0], v[1], v[2], v[3]);
+    else return make_float4(bf16_to_f32(v[0]), bf16_to_f32(v[1]), bf16_to_f32(v[2]), bf16_to_f32(v[3]));
 }
 
 // sum over the LPC lanes of a segment (a fixed butterfly; every lane of the
@@ -48,9 +46,9 @@ __device__ __forceinline__ float seg_sum(float v)
     return v;
 }
 
-// VEC: P % 4 == 0 and 16-byte (fp32) / 8-byte (bf16) aligned rows.
-// LPC: lanes per channel (64, or 16 for planes of at most 64 positions)
-template <typename T, bool VEC, int LPC>
+// LPC: lanes per channel (64, or 16 for planes of at most 64 positions);
+// kLoads: 16-byte loads of each operand in flight per lane (0: single elements)
+template <typename T, int LPC, int kLoads, bool NT>
 __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict__ xh, const T *__restrict__ B,
                                                              i64 C, i64 P, int cblocks, float scale,
                                                              float *__restrict__ gg, float *__restrict__ gbt,
@@ -63,6 +61,7 @@ __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict
     const int wave = threadIdx.x >> 6;
     constexpr int SEGS = 64 / LPC;                 // channels a wave takes at once
     const int seg = lane / LPC, sl = lane % LPC;
+    const i64 P4 = P & ~i64(3);
     float sq = 0.0f;
     for (int k = wave * SEGS; k < kChanPerBlock; k += kWaves * SEGS) {
         const i64 c = (i64)cb * kChanPerBlock + k + seg;
@@ -70,19 +69,35 @@ __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict
         const T *x = xh + (n * C + (live ? c : 0)) * P;
         const T *b = B + (n * C + (live ? c : 0)) * P;
         float ag = 0.0f, ab = 0.0f;
-        if (live) {
-            if (VEC) {
-                for (i64 p = 4 * sl; p < P; p += 4 * LPC) {
-                    const float4 bv = ld4<T>(b + p), xv = ld4<T>(x + p);
-                    ag += bv.x * xv.x + bv.y * xv.y + bv.z * xv.z + bv.w * xv.w;
-                    ab += bv.x + bv.y + bv.z + bv.w;
+        if (live && kLoads == 0) {
+            for (i64 p = sl; p < P; p += LPC) {
+                const float bv = load_elem<T>(b, p);
+                ag += bv * load_elem<T>(x, p);
+                ab += bv;
+            }
+        }
+        if (live && kLoads > 0) {
+            constexpr int L = kLoads > 0 ? kLoads : 1;
+            for (i64 p0 = 4 * sl; p0 < P4; p0 += 4 * LPC * L) {
+                float4 bv[L], xv[L];
+#pragma unroll
+                for (int k = 0; k < L; ++k) {
+                    const i64 p = p0 + 4 * LPC * k < P4 ? p0 + 4 * LPC * k : p0;
+                    bv[k] = ld4<T, NT>(b + p);
+                    xv[k] = ld4<T, NT>(x + p);
                 }
-            } else {
-                for (i64 p = sl; p < P; p += LPC) {
-                    const float bv = load_elem<T>(b, p);
-                    ag += bv * load_elem<T>(x, p);
-                    ab += bv;
+#pragma unroll
+                for (int k = 0; k < L; ++k) {
+                    const bool in = p0 + 4 * LPC * k < P4;
+                    const float g = (bv[k].x * xv[k].x + bv[k].y * xv[k].y) + (bv[k].z * xv[k].z + bv[k].w * xv[k].w);
+                    ag += in ? g : 0.0f;
+                    ab += in ? (bv[k].x + bv[k].y) + (bv[k].z + bv[k].w) : 0.0f;
                 }
+            }
+            if (P4 + sl < P) {
+                const float bv = load_elem<T>(b, P4 + sl);
+                ag += bv * load_elem<T>(x, P4 + sl);
+                ab += bv;
             }
         }
         ag = seg_sum<LPC>(ag);
@@ -107,20 +122,25 @@ __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict
 }
 
 template <typename T>
-void launch_gn(bool vec, bool narrow, dim3 grid, const void *xh, const void *B, i64 C, i64 P, int cblocks,
-               float scale, float *gg, float *gbt, float *sqout, int direct, hipStream_t stream)
+void launch_gn(dim3 grid, const void *xh, const void *B, i64 C, i64 P, int cblocks, float scale,
+               float *gg, float *gbt, float *sqout, int direct, hipStream_t stream)
 {
     const T *x = (const T *)xh, *b = (const T *)B;
-    if (vec && narrow)
-        gn_affine_kernel<T, true, 16><<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout, direct);
-    else if (vec)
-        gn_affine_kernel<T, true, 64><<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout, direct);
-    else if (narrow)
-        gn_affine_kernel<T, false, 16><<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout,
-                                                                      direct);
-    else
-        gn_affine_kernel<T, false, 64><<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout,
-                                                                      direct);
+    const auto go = [&](auto kernel) {
+        kernel<<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout, direct);
+    };
+    // Inputs of whole cache lines per channel, too large to be still cached, go
+    // past the caches: 512 x 64 x 1024 fp32 (268 MB) 45 us against 52; but 32 x
+    // 16 x 4096 (17 MB) 15 against 10, and channels that share lines (300 x
+    // 59 x 989 bf16) 19 against 15.
+    const bool lines = P * sizeof(T) % 128 == 0 && aligned(xh, 128) && aligned(B, 128);
+    const double bytes = 2.0 * (double)(grid.x / cblocks) * (double)C * (double)P * sizeof(T);
+    if (P <= 64 && P % 4 != 0) go(gn_affine_kernel<T, 16, 0, false>);
+    else if (P <= 64) go(gn_affine_kernel<T, 16, 1, false>);
+    else if (P < 260) go(gn_affine_kernel<T, 64, 1, false>);
+    else if (P < 516) go(gn_affine_kernel<T, 64, 2, false>);
+    else if (lines && bytes >= 96e6) go(gn_affine_kernel<T, 64, 4, true>);
+    else go(gn_affine_kernel<T, 64, 4, false>);
 }
 
 }  // namespace
@@ -153,11 +173,8 @@ extern "C" dp_status dp_grad_sample_groupnorm(const void *xhat, const void *B, d
     float *sqout = sqnorm ? (direct ? sqnorm : (float *)ws) : nullptr;
     const dim3 grid((unsigned)(N * cblocks));
     const bool bf = dt == DP_BF16;
-    const bool vec = P % 4 == 0 && aligned(xhat, bf ? 8 : 16) && aligned(B, bf ? 8 : 16);
-    const bool narrow = P <= 64;                   // four channels per wave, 16 lanes each
-    if (bf) launch_gn<uint16_t>(vec, narrow, grid, xhat, B, C, P, cblocks, scale, ggamma, gbeta, sqout, direct,
-                                stream);
-    else launch_gn<float>(vec, narrow, grid, xhat, B, C, P, cblocks, scale, ggamma, gbeta, sqout, direct, stream);
+    if (bf) launch_gn<uint16_t>(grid, xhat, B, C, P, cblocks, scale, ggamma, gbeta, sqout, direct, stream);
+    else launch_gn<float>(grid, xhat, B, C, P, cblocks, scale, ggamma, gbeta, sqout, direct, stream);
     if (sqnorm && !direct) sum_partials((const float *)ws, N, cblocks, sqnorm, stream);
     return launch_status();
 }
