@@ -238,6 +238,165 @@ __global__ __launch_bounds__(kThreads) void emb_clipsum_kernel(
     }
 }
 
+// The same clipped sum in one launch, for vocabularies and rows per sample in
+// the range of emb_scan_ok.  The index of 64 samples is not laid out in
+// memory: workgroup b owns the ids v = b mod G, reads all stored ids of the
+// chunk (each wave four samples at a time, eight independent loads per lane
+// in flight; they come from L2), keeps the row numbers of its own ids in LDS,
+// and its waves then add their rows as emb_clipsum_kernel does, in the same
+// order.  Ids are dealt to the workgroups in turn because the frequent ones
+// of a text vocabulary are neighbours, and each of those has a row in every
+// sample.
+// What bounds it: the chain row_ptr -> ids -> rows (latency), where the
+// laid-out index adds two launches per 64 samples and 512 V bytes of traffic.
+// 64 samples of 256 Zipf ids, V = 10000, D = 100: 13.4 -> 10.4 us, 256 such
+// samples 56.9 -> 34.4; 200 samples of 100 ids, V = 65000, D = 16 95.2 -> 35.7.
+// Tried: 512 workgroups (14.6 and 47.6 us at the first two, 47.9 at the last:
+// a workgroup's start and its scan cost more than its shorter share of ids
+// gives back).
+constexpr int kScanThreads = 1024;
+constexpr int kScanWaves = kScanThreads / 64;
+constexpr int kScanLogGroups = 8;
+constexpr int kScanGroups = 1 << kScanLogGroups;   // workgroups (one per CU), fewer if V is less
+constexpr int kScanIds = 256;          // ids per workgroup, at most (64 KB of LDS)
+constexpr int kScanSamples = kChunk / kScanWaves;
+
+// acc += c * row over up to BATCH hit lanes of mask, in ascending order; slots
+// past the last hit repeat the first (a valid row) and are not added
+template <int VEC, int BATCH>
+__device__ __forceinline__ void add_hit_rows(uint64_t &mask, int hit, float cn, const float *__restrict__ rows, i64 D,
+                                             i64 c, float (&acc)[VEC])
+{
+    int kk[BATCH];
+    float cj[BATCH];
+    bool ok[BATCH];
+    const int first_hit = __ffsll((unsigned long long)mask) - 1;
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+        ok[j] = mask != 0;
+        const int b = __builtin_amdgcn_readfirstlane(ok[j] ? __ffsll((unsigned long long)mask) - 1 : first_hit);
+        mask &= mask - 1;
+        kk[j] = __builtin_amdgcn_readlane(hit, b);
+        cj[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cn), b));
+    }
+    float x[BATCH][VEC];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+        const float *src = rows + (i64)kk[j] * D + c;
+        if constexpr (VEC == 4) {
+            const float4 q = *reinterpret_cast<const float4 *>(src);
+            x[j][0] = q.x; x[j][1] = q.y; x[j][2] = q.z; x[j][3] = q.w;
+        } else {
+            x[j][0] = src[0];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j)
+        if (ok[j])
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] += cj[j] * x[j][i];
+}
+
+template <int VEC>
+__global__ __launch_bounds__(kScanThreads) void emb_clipsum_scan_kernel(
+    const int64_t *__restrict__ row_ptr, const int64_t *__restrict__ uniq, const float *__restrict__ rows, i64 cap,
+    const float *__restrict__ norm, float C, i64 N, int V, i64 D, float *__restrict__ sum, int32_t *status)
+{
+    __shared__ int32_t idx[kScanIds * kChunk];           // [local id][sample of the chunk]: row number, -1 for none
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int G = kScanGroups;
+    const int b = blockIdx.x;
+    const int nloc = (V - b + G - 1) / G;                // ids b, b + G, ... below V (b < V)
+    for (i64 n0 = 0; n0 < N; n0 += kChunk) {
+        const int nc = (int)(N - n0 < kChunk ? N - n0 : kChunk);
+        i64 k[kScanSamples], end[kScanSamples];
+#pragma unroll
+        for (int q = 0; q < kScanSamples; ++q) {
+            const int m = wv + kScanWaves * q;
+            const bool in = m < nc;
+            const i64 hi = in ? row_ptr[n0 + m + 1] : 0;
+            k[q] = (in ? row_ptr[n0 + m] : 0) + lane;
+            end[q] = hi < cap ? hi : cap;
+            if (hi > cap && b == 0 && lane == 0) raise_flag(status, DP_FLAG_CAP);
+        }
+        const float cn = lane < nc ? clip_factor(norm[n0 + lane], C) : 0.0f;
+        for (int i = tid; i < nloc * kChunk; i += kScanThreads) idx[i] = -1;
+        __syncthreads();
+        bool more = true;
+        while (more) {
+            int64_t v[2][kScanSamples];
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int q = 0; q < kScanSamples; ++q) v[r][q] = k[q] + 64 * r < end[q] ? uniq[k[q] + 64 * r] : 0;
+            bool left = false;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int q = 0; q < kScanSamples; ++q) {
+                    if (k[q] + 64 * r >= end[q]) continue;
+                    if (v[r][q] < 0 || v[r][q] >= V) {
+                        if (b == 0) raise_flag(status, DP_FLAG_BAD_INDEX);
+                    } else if (((int)v[r][q] & (G - 1)) == b) {
+                        idx[((int)v[r][q] >> kScanLogGroups) * kChunk + wv + kScanWaves * q] = (int32_t)(k[q] + 64 * r);
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < kScanSamples; ++q) {
+                k[q] += 128;
+                left |= k[q] < end[q];
+            }
+            more = __ballot(left) != 0;
+        }
+        __syncthreads();
+        for (int l = wv; l < nloc; l += kScanWaves) {
+            const int hit = idx[l * kChunk + lane];
+            const uint64_t all = __ballot(hit >= 0);
+            if (n0 > 0 && all == 0) continue;
+            const i64 at = ((i64)l * G + b) * D;
+            for (i64 c0 = 0; c0 < D; c0 += 64 * VEC) {
+                const i64 c = c0 + (i64)VEC * lane;
+                const bool on = c < D;
+                const i64 cc = on ? c : 0;
+                float acc[VEC];
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
+                if (n0 > 0 && on) {
+                    if constexpr (VEC == 4) {
+                        const float4 q = *reinterpret_cast<const float4 *>(sum + at + c);
+                        acc[0] = q.x; acc[1] = q.y; acc[2] = q.z; acc[3] = q.w;
+                    } else {
+                        acc[0] = sum[at + c];
+                    }
+                }
+                uint64_t mask = all;
+                while (mask) {
+                    if (__popcll(mask) > 4) add_hit_rows<VEC, 16>(mask, hit, cn, rows, D, cc, acc);
+                    else add_hit_rows<VEC, 4>(mask, hit, cn, rows, D, cc, acc);
+                }
+                if (on) {
+                    if constexpr (VEC == 4)
+                        *reinterpret_cast<float4 *>(sum + at + c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                    else
+                        sum[at + c] = acc[0];
+                }
+            }
+        }
+        __syncthreads();                                 // the index is rewritten by the next chunk
+    }
+}
+
+// Every workgroup reads every stored id, so the scan pays while they are few
+// (up to 256 rows per sample, which cap bounds) and one workgroup per CU holds
+// the index of all ids.  64 samples with 256 distinct ids each: V = 10000 12.9
+// (index) against 9.8 us, V = 50000 22.4 against 16.6; with 512 each, V =
+// 10000: 12.7 against 14.5.
+bool emb_scan_ok(i64 N, i64 V, i64 cap)
+{
+    return V <= kScanGroups * kScanIds && cap <= 256 * N;
+}
+
 }  // namespace
 }  // namespace dpg
 
@@ -350,6 +509,16 @@ extern "C" dp_status dp_clip_accumulate_embedding(const int64_t *row_ptr, const 
     DPG_REQUIRE(need == 0 || aligned(ws, 16), DP_EINVAL);
     if (N == 0) {
         zero_fill(sum, V * D, stream);
+        return launch_status();
+    }
+    if (emb_scan_ok(N, V, cap)) {
+        const unsigned grid = (unsigned)(V < kScanGroups ? V : kScanGroups);
+        if (D % 4 == 0 && aligned(rows, 16) && aligned(sum, 16))
+            emb_clipsum_scan_kernel<4><<<grid, kScanThreads, 0, stream>>>(row_ptr, uniq_ids, rows, cap, norm, C, N,
+                                                                          (int)V, D, sum, status);
+        else
+            emb_clipsum_scan_kernel<1><<<grid, kScanThreads, 0, stream>>>(row_ptr, uniq_ids, rows, cap, norm, C, N,
+                                                                          (int)V, D, sum, status);
         return launch_status();
     }
     int32_t *map = (int32_t *)ws;
