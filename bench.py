@@ -86,13 +86,13 @@ def call_costs(st, nnz=None):
                                          "outer_kernel", None)
             else:
                 staged = bf_mfma and L.T % 32 == 0
-                # fp32 operands whose rows are 16-byte multiples over T % 16 == 0 are staged straight into LDS
-                staged32 = not bf and L.T % 16 == 0 and L.d_in % 4 == 0 and L.d_out % 4 == 0
+                # rows of at least 16 bytes: fp32 operands as three bf16 parts, bf16 ones as they are
+                split = min(L.d_in, L.d_out) >= (8 if bf else 4)
                 out["grad:" + L.name] = (N * L.T * (L.d_in + L.d_out) * e + grads + N * 4,
                                          2 * N * L.T * L.d_in * L.d_out,
                                          "bf16_grad_sample_kernel" if staged else
                                          "bf16_per_sample_kernel" if bf_mfma else
-                                         "ps_gemm_dma_kernel" if staged32 else "ps_gemm_kernel",
+                                         "ps_split_kernel" if split else "ps_gemm_kernel",
                                          "bf16" if bf_mfma else "f32")
             if lb.clip_mode == "fused":
                 # all fused Linear layers' weight sums share one grouped call; their
@@ -114,7 +114,9 @@ def call_costs(st, nnz=None):
             choice = dp.dp_conv2d_kernel_choice(N, L.c_in, L.h, L.w, L.c_out, L.k[0], L.k[1], L.stride[0],
                                                 L.stride[1], L.pad[0], L.pad[1])
             kname = {dp.DP_CONV_KERNEL_SMALL: "conv_small_kernel",
-                     dp.DP_CONV_KERNEL_ROWS: "conv_rows_kernel"}.get(choice, "conv_per_sample_kernel")
+                     # (the row chunks run on either matrix unit, by the layer's sizes)
+                     dp.DP_CONV_KERNEL_ROWS: "conv_rows_kernel+conv_split_kernel"}.get(choice,
+                                                                                       "conv_per_sample_kernel")
             out["grad:" + L.name] = (N * (L.c_in * L.h * L.w + L.c_out * ho * wo) * e + grads + N * 4,
                                      2 * N * L.c_out * kk * ho * wo, kname, "f32")
             col_bytes += grads
@@ -125,6 +127,7 @@ def call_costs(st, nnz=None):
                                      N * L.T * L.D, "emb_fused_kernel" if L.T <= 512 else "emb_csr_kernel", None)
             # reads row_ptr, the ids, the rows and the norms; writes the dense [V][D] sum
             out["clip:" + L.name] = ((N + 1) * 8 + u * (L.D * 4 + 8) + N * 4 + L.V * L.D * 4, 2 * u * L.D,
+                                     "emb_clipsum_scan_kernel" if L.V <= 65536 and L.T <= 256 else
                                      "emb_clipsum_kernel", None)
         elif isinstance(L, W.LSTMRecurrence):
             # reads the stored gates and cell states, W_hh and dh_last; writes the gate backprop
@@ -151,9 +154,9 @@ def call_costs(st, nnz=None):
             gb_ += b0
             gf_ += f0
             kinds.add({"bf16_grad_sample_kernel": "bf16_grad_group_kernel",
-                       "ps_gemm_dma_kernel": "ps_dma_group_kernel"}.get(kn, "grad_many_kernel"))
+                       "ps_split_kernel": "ps_split_group_kernel"}.get(kn, "grad_many_kernel"))
         kname = "+".join(sorted(kinds))
-        mt = "bf16" if "bf16_grad_group_kernel" in kinds else "f32" if "ps_dma_group_kernel" in kinds else None
+        mt = "bf16" if "bf16_grad_group_kernel" in kinds else "f32" if "ps_split_group_kernel" in kinds else None
         out["grad:group"] = (gb_, gf_, kname, mt)
     if not st.fold_norms:
         out["norms"] = (len(st.layers) * N * 4 + N * 4, len(st.layers) * N, "norms_kernel", None)
@@ -179,6 +182,7 @@ KERNEL_SOURCES = {
     "ghost_gram_kernel": ["paper_2109_12298_amd/csrc/ghost.hip", "paper_2109_12298_amd/csrc/bf16_stage.hpp"],
     "gn_affine_kernel": ["paper_2109_12298_amd/csrc/groupnorm.hip"],
     "conv_rows_kernel": ["paper_2109_12298_amd/csrc/conv2d_rows.hip"],
+    "conv_split_kernel": ["paper_2109_12298_amd/csrc/conv2d_split.hip", "paper_2109_12298_amd/csrc/split_bf16.hpp"],
     "conv_small_kernel": ["paper_2109_12298_amd/csrc/conv2d_small.hip",
                           "paper_2109_12298_amd/csrc/conv2d_small_dev.hpp"],
     "grad_many_kernel": ["paper_2109_12298_amd/csrc/grad_many.hip", "paper_2109_12298_amd/csrc/conv2d_small_dev.hpp",
@@ -192,14 +196,15 @@ KERNEL_SOURCES = {
     "bf16_grad_group_kernel": ["paper_2109_12298_amd/csrc/grad_sample_bf16.hip",
                                "paper_2109_12298_amd/csrc/bf16_stage.hpp", "paper_2109_12298_amd/csrc/grad_many.hip"],
     "ps_gemm_kernel": ["paper_2109_12298_amd/csrc/linear.hip"],
-    "ps_gemm_dma_kernel": ["paper_2109_12298_amd/csrc/linear.hip", "paper_2109_12298_amd/csrc/bf16_stage.hpp"],
-    "ps_dma_group_kernel": ["paper_2109_12298_amd/csrc/linear.hip", "paper_2109_12298_amd/csrc/bf16_stage.hpp",
-                            "paper_2109_12298_amd/csrc/linear_staged.hpp", "paper_2109_12298_amd/csrc/grad_many.hip"],
+    "ps_split_kernel": ["paper_2109_12298_amd/csrc/ps_split.hip", "paper_2109_12298_amd/csrc/split_bf16.hpp"],
+    "ps_split_group_kernel": ["paper_2109_12298_amd/csrc/ps_split.hip", "paper_2109_12298_amd/csrc/split_bf16.hpp",
+                              "paper_2109_12298_amd/csrc/grad_many.hip"],
     "clipsum_gemm_kernel": ["paper_2109_12298_amd/csrc/linear.hip", "paper_2109_12298_amd/csrc/mfma_tile.hpp"],
     "conv_per_sample_kernel": ["paper_2109_12298_amd/csrc/conv2d.hip", "paper_2109_12298_amd/csrc/mfma_tile.hpp"],
     "colsum_kernel": ["paper_2109_12298_amd/csrc/clip.hip"],
     "emb_csr_kernel": ["paper_2109_12298_amd/csrc/embedding.hip"],
     "emb_fused_kernel": ["paper_2109_12298_amd/csrc/embedding.hip"],
+    "emb_clipsum_scan_kernel": ["paper_2109_12298_amd/csrc/clip.hip"],
     "emb_clipsum_kernel": ["paper_2109_12298_amd/csrc/clip.hip"],
     "ln_partial_kernel": ["paper_2109_12298_amd/csrc/layernorm.hip"],
     "ln_rows_kernel": ["paper_2109_12298_amd/csrc/layernorm.hip"],
