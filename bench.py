@@ -182,7 +182,9 @@ KERNEL_SOURCES = {
     "ghost_gram_kernel": ["paper_2109_12298_amd/csrc/ghost.hip", "paper_2109_12298_amd/csrc/bf16_stage.hpp"],
     "gn_affine_kernel": ["paper_2109_12298_amd/csrc/groupnorm.hip"],
     "conv_rows_kernel": ["paper_2109_12298_amd/csrc/conv2d_rows.hip"],
-    "conv_split_kernel": ["paper_2109_12298_amd/csrc/conv2d_split.hip", "paper_2109_12298_amd/csrc/split_bf16.hpp"],
+    "conv_split_kernel": ["paper_2109_12298_amd/csrc/conv2d_split.hip",
+                          "paper_2109_12298_amd/csrc/conv2d_split_plan.hpp",
+                          "paper_2109_12298_amd/csrc/split_bf16.hpp"],
     "conv_small_kernel": ["paper_2109_12298_amd/csrc/conv2d_small.hip",
                           "paper_2109_12298_amd/csrc/conv2d_small_dev.hpp"],
     "grad_many_kernel": ["paper_2109_12298_amd/csrc/grad_many.hip", "paper_2109_12298_amd/csrc/conv2d_small_dev.hpp",

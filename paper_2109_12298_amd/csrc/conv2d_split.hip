@@ -41,6 +41,7 @@
 #include "common.hpp"
 #include "split_bf16.hpp"
 #include "conv2d_split.hpp"
+#include "conv2d_split_plan.hpp"
 
 namespace dpg {
 namespace {
@@ -49,39 +50,12 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 using split::finite_f32;
+using namespace csplit;
 
 constexpr int kThreads = 256, kWaves = 4;
-constexpr int kT = 3;                  // tap rows and columns per group, at most
 constexpr int kBatch = 2;              // units per thread loaded at once
-constexpr int kMaxGroups = 64;
-constexpr size_t kLds = 76 * 1024;     // two workgroups per CU
-
-struct ConvGroup {
-    int8_t u0, ul;                     // tap rows u0 .. u0 + ul - 1
-    int8_t vc, vl;                     // center tap column, 1: it, 2: and vc + sw, 3: and vc - sw
-    int16_t sc, phase;                 // vc - pw = sw * sc + phase, 0 <= phase < sw
-};
-
-struct SplitShape {
-    int Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw;
-    int L, khw;
-    int NU, inv_nu;                    // units per row, ceil(65536 / NU)
-    int gl, inv_gl, gp;                // GY units loaded per row, ceil(65536 / gl), row pitch: NU and NU + 1 (a zero
-                                       // guard before each row) where a row's neighbours past its ends are zero
-                                       // for every group, else both NU + 2 (they are loaded)
-    int RC, XR;                        // output rows per chunk, input rows they read
-    int csx, csg;                      // channel strides in LDS (bytes)
-    int px, pg;                        // plane strides (bytes)
-    int nx, ng;                        // units per chunk of X and GY
-    int inv_xrow, inv_grow;            // ceil(2^20 / (XR * NU)), ceil(2^20 / (RC * gl))
-    int nci, nco, ngrp, gpw, tiles;    // channel tiles, groups, groups per workgroup, workgroups per sample
-    int bias_at;                       // byte offset of the bias sums (one float per GY unit of a chunk), 0: none
-    int full;                          // kh == kw == 3 in one group with stores by rows
-    ConvGroup g[kMaxGroups];
-};
-
-// floor(i / d) from ceil(2^20 / d), exact while i * d < 2^20
-__device__ __forceinline__ int div20(int i, int inv) { return (int)(((uint32_t)i * (uint32_t)inv) >> 20); }
+// output staging of two blocks (the hand-over needs less)
+constexpr size_t kLeastLds = 2 * 32 * 289 * 4;
 
 template <typename T>
 struct Unit {
@@ -213,9 +187,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
         const int u0 = s.g[gi].u0, ul = s.g[gi].ul, vc = s.g[gi].vc, vl = s.g[gi].vl;
         const int sc = s.g[gi].sc, phase = s.g[gi].phase;
 
-        const bool clip_x = (s.W % (8 * s.sw)) != 0, clip_g = sc != 0 || s.NU * 8 != s.Wo;
-        // One chunk into LDS: X unit i = (ci, row, unit), GY unit i = (co, row,
-        // unit), kBatch of them per thread in flight.  Nothing of it stays in
+        const bool clip_x = clips_x(s), clip_g = clips_g(s, sc);
+        // One chunk into LDS, kBatch units per thread in flight.  Nothing of it stays in
         // registers while the chunk is multiplied (the accumulators leave room
         // for the operands only); the CU's other workgroup multiplies meanwhile.
         // the first input channel tile also adds GY's units up, each thread its own
@@ -228,13 +201,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
                 int at[kBatch], col[kBatch], e[kBatch];
 #pragma unroll
                 for (int q = 0; q < kBatch; ++q) {
-                    const int i = base + t + kThreads * q, c = div20(i, s.inv_xrow), w = i - c * (s.XR * s.NU);
-                    const int r = (w * s.inv_nu) >> 16, cu = w - r * s.NU, ih = oh0 * s.sh + r + u0 - s.ph;
-                    at[q] = i < s.nx ? c * s.csx + w * 16 : -1;
-                    col[q] = 8 * cu * s.sw + phase;
-                    e[q] = ((ci0 + c) * s.H + ih) * s.W + col[q];
-                    load_unit<T>(rx, e[q], s.sw, s.Cin * s.H * s.W,
-                                 (uint32_t)ih >= (uint32_t)s.H || ci0 + c >= s.Cin || i >= s.nx, u[q]);
+                    const UnitAt a = x_unit(s, u0, phase, ci0, oh0, base + t + kThreads * q);
+                    at[q] = a.at;
+                    col[q] = a.col;
+                    e[q] = a.e;
+                    load_unit<T>(rx, a.e, s.sw, s.Cin * s.H * s.W, a.dead, u[q]);
                 }
 #pragma unroll
                 for (int q = 0; q < kBatch; ++q) {
@@ -250,12 +221,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
                 int at[kBatch], col[kBatch], e[kBatch];
 #pragma unroll
                 for (int q = 0; q < kBatch; ++q) {
-                    const int i = base + t + kThreads * q, c = div20(i, s.inv_grow), w = i - c * (s.RC * s.gl);
-                    const int r = (w * s.inv_gl) >> 16, cu = w - r * s.gl, oh = oh0 + r;
-                    at[q] = i < s.ng ? c * s.csg + (r * s.gp + cu + s.gp - s.gl) * 16 : -1;
-                    col[q] = 8 * (cu + s.gp - s.gl - 1) - sc;
-                    e[q] = ((co0 + c) * s.Ho + oh) * s.Wo + col[q];
-                    load_unit<T>(rg, e[q], 1, s.Cout * s.L, oh >= s.Ho || co0 + c >= s.Cout || i >= s.ng, u[q]);
+                    const UnitAt a = g_unit(s, sc, co0, oh0, base + t + kThreads * q);
+                    at[q] = a.at;
+                    col[q] = a.col;
+                    e[q] = a.e;
+                    load_unit<T>(rg, a.e, 1, s.Cout * s.L, a.dead, u[q]);
                 }
 #pragma unroll
                 for (int q = 0; q < kBatch; ++q) {
@@ -546,128 +516,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-struct Layout {
-    int wi, wo, wk;
-};
-constexpr Layout kLayouts[] = {{1, 2, 1}, {2, 1, 1}, {1, 1, 2}};
-// output staging of two blocks (the hand-over needs less)
-constexpr size_t kLeastLds = 2 * 32 * 289 * 4;
-
-int odd_units(int bytes) { return (((bytes + 15) / 16) | 1) * 16; }
-
-bool plan(const ConvRowsArgs &a, bool bf16, int slots, const Layout &w, SplitShape &s)
-{
-    s.Cin = (int)a.Cin; s.H = (int)a.H; s.W = (int)a.W; s.Cout = (int)a.Cout; s.Ho = (int)a.Ho; s.Wo = (int)a.Wo;
-    s.kh = (int)a.kh; s.kw = (int)a.kw; s.sh = (int)a.sh; s.sw = (int)a.sw; s.ph = (int)a.ph; s.pw = (int)a.pw;
-    s.L = s.Ho * s.Wo;
-    s.khw = s.kh * s.kw;
-    const int np = bf16 ? 1 : 3;
-    // columns of one phase, and room for the outputs that only reach padding
-    const int cols = (s.W + s.sw - 1) / s.sw;
-    s.NU = (cols + 7) / 8;
-    s.inv_nu = (65536 + s.NU - 1) / s.NU;
-    s.nci = (s.Cin + 32 * w.wi - 1) / (32 * w.wi);
-    s.nco = (s.Cout + 32 * w.wo - 1) / (32 * w.wo);
-    // tap groups: rows in balanced threes; columns of one phase in balanced threes
-    s.ngrp = 0;
-    bool all3 = true, zero_ends = true;
-    const int nu = (s.kh + kT - 1) / kT;
-    for (int i = 0; i < nu; ++i) {
-        const int u0 = i * s.kh / nu, u1 = (i + 1) * s.kh / nu;
-        for (int f = 0; f < s.sw && f < s.kw; ++f) {
-            const int nv = (s.kw - f + s.sw - 1) / s.sw, parts = (nv + kT - 1) / kT;   // v = f, f + sw, ...
-            for (int j = 0; j < parts; ++j) {
-                const int v0 = j * nv / parts, v1 = (j + 1) * nv / parts, vl = v1 - v0;
-                if (s.ngrp == kMaxGroups) return false;
-                const int vc = f + s.sw * (v0 + (vl == 3 ? 1 : 0));
-                const int dv = vc - s.pw, sc = dv >= 0 ? dv / s.sw : -((s.sw - 1 - dv) / s.sw);
-                s.g[s.ngrp++] = {(int8_t)u0, (int8_t)(u1 - u0), (int8_t)vc, (int8_t)vl, (int16_t)sc, (int16_t)(dv - sc * s.sw)};
-                all3 = all3 && vl == 3 && u1 - u0 == 3;
-                // GY[-1 - sc] and GY[8 NU - sc] are outside the row
-                zero_ends = zero_ends && (vl == 1 || (sc >= 0 && 8 * s.NU - sc >= s.Wo));
-            }
-        }
-    }
-    s.gl = zero_ends ? s.NU : s.NU + 2;
-    s.gp = zero_ends ? s.NU + 1 : s.NU + 2;
-    s.inv_gl = (65536 + s.gl - 1) / s.gl;
-    s.full = all3 ? (s.kh == 3 && s.kw == 3 && s.sw == 1 ? 2 : 1) : 0;
-    const int room = slots / (s.nci * s.nco);
-    if (room < 1) return false;
-    s.gpw = (s.ngrp + room - 1) / room;
-    s.tiles = s.nci * s.nco * ((s.ngrp + s.gpw - 1) / s.gpw);
-    // every column of GY is in exactly one unit of the first group
-    const int first = -8 * (s.gp - s.gl - 1) + s.g[0].sc;
-    const bool covers = first >= 0 && 8 * s.gl - first >= s.Wo;
-    // the most output rows per chunk that fit
-    s.RC = 0;
-    for (int rc = s.Ho < 64 ? s.Ho : 64; rc >= 1; --rc) {
-        const int xr = (rc - 1) * s.sh + (s.kh < kT ? s.kh : kT);
-        const i64 nx = (i64)32 * w.wi * xr * s.NU, ng = (i64)32 * w.wo * rc * s.gl;
-        if ((i64)xr * s.NU * nx >= (1 << 20) || (i64)rc * s.gl * ng >= (1 << 20)) continue;   // div20
-        // an odd number of units leaves one step a unit past the chunk: it reads
-        // X at row (rc - 1) * sh + 2 + sh (any finite value) and GY's two units
-        // from rc * gp + 1 on (zeros)
-        const int csx = odd_units(((xr + s.sh - 1) * s.NU + 1) * 16), csg = odd_units((rc * s.gp + 3) * 16);
-        const int px = 32 * w.wi * csx, pg = 32 * w.wo * csg;
-        const i64 total = (i64)np * (px + pg) + (covers ? 4 * ng : 0);
-        if (total > (i64)kLds) continue;
-        const int chunks = (s.Ho + rc - 1) / rc, even = (s.Ho + chunks - 1) / chunks;
-        if (even < rc) {                                 // the same number of chunks, of equal size
-            rc = even + 1;
-            continue;
-        }
-        s.bias_at = covers ? np * (px + pg) : 0;
-        s.RC = rc; s.XR = xr; s.csx = csx; s.csg = csg; s.px = px; s.pg = pg; s.nx = (int)nx; s.ng = (int)ng;
-        break;
-    }
-    if (s.RC == 0) return false;
-    s.inv_xrow = ((1 << 20) + s.XR * s.NU - 1) / (s.XR * s.NU);
-    s.inv_grow = ((1 << 20) + s.RC * s.gl - 1) / (s.RC * s.gl);
-    return true;
-}
-
-// A plan's time in cycles, from measured parts: a workgroup's start, output and
-// end; per chunk the staging's round trip and its units (256 threads, the
-// splitting of one unit each); per step the MFMAs of the wave with more taps.
-// Two workgroups share a CU: one stages while the other multiplies.
-double cost_of(const SplitShape &s, const Layout &w, i64 N, bool bf16)
-{
-    const int chunks = (s.Ho + s.RC - 1) / s.RC, steps = ((s.RC * s.NU + 1) / 2 + w.wk - 1) / w.wk;
-    const double units = (s.nx + 255) / 256 + (s.ng + 255) / 256, np = bf16 ? 1 : 6;
-    double c = 0;
-    for (int i = 0; i < s.ngrp; ++i) {
-        const int taps = s.g[i].vl == 3 ? (3 * s.g[i].ul + 1) / 2 : s.g[i].vl == 2 ? s.g[i].ul : (s.g[i].ul + 1) / 2;
-        const double mult = steps * (taps * np * 32.0 + 120.0), stage = 3000.0 + units * (bf16 ? 400.0 : 600.0);
-        c += chunks * (2 * mult > stage ? mult + (stage > mult ? stage : mult) : mult + stage) + 6000.0;
-    }
-    const double groups = (double)s.ngrp / s.gpw;
-    const double rounds = (double)N * s.tiles / 512.0;
-    return (c / groups + 8000.0) * (rounds > 1.0 ? rounds : 1.0);
-}
-
-bool choose(const ConvRowsArgs &a, bool bf16, int slots, SplitShape &best, int &which)
-{
-    // 32-bit offsets, taps in eight bits, and the quotients of inv_nu and div20
-    if (a.kh > 100 || a.kw > 100 || a.W > 2048 || a.Cin * a.H * a.W >= (i64(1) << 28) ||
-        a.Cout * a.Ho * a.Wo >= (i64(1) << 28) || a.Cin * a.kh * a.kw * a.Cout >= (i64(1) << 30) || a.ph > a.H + a.kh ||
-        a.pw > 1024 || a.ph > 1024 || a.H > (1 << 20))
-        return false;
-    which = -1;
-    double cost = 0;
-    for (int k = 0; k < (int)(sizeof(kLayouts) / sizeof(kLayouts[0])); ++k) {
-        SplitShape s;
-        if (!plan(a, bf16, slots, kLayouts[k], s)) continue;
-        const double c = cost_of(s, kLayouts[k], a.N, bf16);
-        if (which < 0 || c < cost) {
-            best = s;
-            which = k;
-            cost = c;
-        }
-    }
-    return which >= 0;
-}
-
 template <typename T, int WI, int WO, int WK>
 void launch(const ConvRowsArgs &a, const SplitShape &s, float scale, float *gW, float *gb, float *sqout,
             hipStream_t stream)
@@ -696,6 +544,11 @@ void dispatch(int which, const ConvRowsArgs &a, const SplitShape &s, float scale
     }
 }
 
+ConvGeom geom(const ConvRowsArgs &a)
+{
+    return {a.N, a.Cin, a.H, a.W, a.Cout, a.Ho, a.Wo, a.kh, a.kw, a.sh, a.sw, a.ph, a.pw};
+}
+
 }  // namespace
 
 // Measured against the row-chunked fp32 MFMA kernel (us, that one / this one).
@@ -721,7 +574,7 @@ bool conv_split_ok(const ConvRowsArgs &a, bool bf16, int slots)
     const double useful = (double)(a.Ho * a.Wo) * fill;
     SplitShape s;
     int which;
-    if (useful < 40.0 || !choose(a, bf16, slots, s, which)) return false;
+    if (useful < 40.0 || !choose(geom(a), bf16, slots, s, which)) return false;
     if (bf16) return useful >= (s.ngrp > 4 ? 90.0 : 40.0);
     if (a.kh != 3 || a.kw != 3) return false;
     if (a.sh == 1 && a.sw == 1) return useful >= 96.0;
@@ -733,7 +586,7 @@ void conv_split_launch(const ConvRowsArgs &a, bool bf16, int slots, float scale,
 {
     SplitShape s;
     int which;
-    if (!choose(a, bf16, slots, s, which)) return;      // conv_split_ok said yes
+    if (!choose(geom(a), bf16, slots, s, which)) return;      // conv_split_ok said yes
     const bool direct = s.tiles == 1;
     s.full = s.full == 2 ? 1 : 0;
     float *sqout = sqnorm ? (direct ? sqnorm : partial) : nullptr;

@@ -120,6 +120,10 @@ CONVS = [
 CONVS_BF16 = CONVS + [
     (3, 24, 40, 27, 27, 5, 2, 2), (2, 40, 24, 13, 14, 5, 1, 0), (1, 24, 24, 19, 21, 7, 1, 3), (2, 26, 33, 21, 26, 4, 2, 1),
     (1, 30, 64, 14, 15, 2, 1, 0), (2, 64, 32, 9, 9, 3, 3, 1),
+    # several tap groups, with rows of GY that fill their units exactly
+    (2, 24, 40, 32, 32, 5, 2, 2), (2, 24, 40, 31, 31, 5, 2, 2), (2, 32, 64, 16, 16, 5, 2, 2), (2, 32, 64, 16, 16, 4, 2, 1),
+    (2, 32, 64, 32, 32, 4, 2, 1), (1, 64, 64, 32, 32, 7, 2, 3), (2, 32, 64, 15, 15, 4, 1, 2), (2, 32, 64, 14, 14, 5, 1, 3),
+    (2, 32, 64, 24, 24, 5, 3, 1),
 ]
 
 
