@@ -347,7 +347,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
         if (s.bias_at) lds_barrier();                    // the output and hand-over staging may lie over the sums
         if constexpr (NP == 3) {
 #pragma unroll
-            for (int x = 0; x < kT + 2; ++x) big[x] += rest[x];
+            for (int x = 0; x < kT + 2; ++x)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) big[x][r] = split::kUnscale * (big[x][r] + rest[x][r]);
         }
         // waves that share a block: partial sums handed over through LDS, in wave order
         if constexpr (WK > 1) {
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
             }
         }
         if (__syncthreads_or(bad)) [[unlikely]] {
-            // An infinity, a NaN or a value past bf16's range among the inputs,
+            // An infinity, a NaN or a value too large to split among the inputs,
             // or outputs whose squares pass fp32's range: the wave's outputs
             // again (the stores above are done: the barrier waits for them),
             // as plain fp32 sums.

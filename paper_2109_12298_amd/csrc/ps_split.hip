@@ -347,7 +347,7 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int j = j0 + wj + 32 * x + 8 * (r >> 2) + 4 * kg + (r & 3), i = i0 + wi + 32 * y + li;
-                const float g = scale * (NP == 3 ? big[x][y][r] + rest[x][y][r] : big[x][y][r]);
+                const float g = scale * (NP == 3 ? split::kUnscale * (big[x][y][r] + rest[x][y][r]) : big[x][y][r]);
                 big[x][y][r] = g;
                 const float v = i < Do && j < Di ? g : 0.0f;
                 sq += v * v;
@@ -355,7 +355,7 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
     float *G = gW + n * dout * din;
     lds_barrier();                                       // the stages' LDS is free
     if (NP == 3 && __any(!finite_f32(sq))) [[unlikely]] {
-        // An infinity, a NaN or a value past bf16's range among the wave's
+        // An infinity, a NaN or a value too large to split among the wave's
         // inputs, or outputs whose squares pass fp32's range: plain fp32 sums
         // in ascending t.
         sq = 0.0f;

@@ -109,6 +109,56 @@ def test_linear_small_magnitudes():
     assert (abs(gW - ref) <= (T + 8) * 2.0 ** -24 * mag + 2.0 ** -140).all()
 
 
+def small_feature_scales(n, e):
+    """2^e for every second feature, 1 for the others."""
+    return torch.where(torch.arange(n) % 2 == 1, 2.0 ** e, 1.0).double()
+
+
+@pytest.mark.parametrize("e", [-114, -120, -126, -133, -140])
+def test_linear_tiny_values(e):
+    """Features of any size, subnormal ones among them, keep fp32's bits: the roundings of the sums alone
+    are left, of which each is at most 2^-24 and K + 8 add in quadrature over independent terms."""
+    N, T, di, do = 2, 64, 66, 130
+    say("linear tiny values", e)
+    g = torch.Generator().manual_seed(16)
+    A = (torch.randn(N, T, di, generator=g).double() * small_feature_scales(di, e)).float()
+    B = torch.randn(N, T, do, generator=g) * 2.0 ** 60
+    gW, _, _ = linear(A, B, 0, scale=1.0)
+    ref = np.einsum("nti,ntj->nij", B.double().numpy(), A.double().numpy())
+    for j in (0, 1):
+        err, size = gW[:, :, j::2] - ref[:, :, j::2], ref[:, :, j::2]
+        assert np.linalg.norm(err) <= (T + 8) ** 0.5 * 2.0 ** -24 * np.linalg.norm(size)
+
+
+@pytest.mark.parametrize("e", [-120, -133])
+def test_conv_tiny_values(e):
+    N, ci, co, H = 2, 40, 36, 14
+    say("conv tiny values", e)
+    g = torch.Generator().manual_seed(17)
+    X = (torch.randn(N, ci, H, H, generator=g).double() * small_feature_scales(ci, e)[:, None, None]).float()
+    GY = torch.randn(N, co, H, H, generator=g) * 2.0 ** 60
+    gW, _, _ = conv(X, GY, 3, 1, 1, 0, 1.0)
+    ref = conv_reference(X, GY, 3, 1, 1, 1.0)[0].reshape(N, co, ci, 9)
+    err = gW.reshape(N, co, ci, 9) - ref
+    for j in (0, 1):
+        assert np.linalg.norm(err[:, :, j::2]) <= (H * H + 8) ** 0.5 * 2.0 ** -24 * np.linalg.norm(ref[:, :, j::2])
+
+
+@pytest.mark.parametrize("value", [2.0 ** 103, 2.0 ** 104, 1e35])
+def test_linear_large_values(value):
+    """On both sides of the magnitude that can be split, with ordinary results."""
+    N, T, di, do = 2, 40, 70, 140
+    say("linear large values", value)
+    g = torch.Generator().manual_seed(18)
+    A, B = torch.randn(N, T, di, generator=g), torch.randn(N, T, do, generator=g) * 2.0 ** -60
+    A[1, 33, 69] = value
+    gW, _, sq = linear(A, B, 0, scale=1.0)
+    ref = np.einsum("nti,ntj->nij", B.double().numpy(), A.double().numpy())
+    mag = np.einsum("nti,ntj->nij", abs(B.double().numpy()), abs(A.double().numpy()))
+    assert (abs(gW - ref) <= (T + 8) * 2.0 ** -24 * mag).all()
+    assert np.isfinite(sq).all()
+
+
 # N, Cin, Cout, H, W, k, stride, pad: the shapes the automatic choice gives the
 # bf16-matrix kernel, at the edges of its channel blocks (32, 64), units of
 # eight columns, row chunks, tap groups and shifts
