@@ -245,10 +245,13 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
         put<SA, E, NP>(L, sa, xa);
         put<SB, E, NP>(L + NP * SA::PLANE, sb, xb);
         if (do_bias && c <= last) {
+            // (a thread's rows are added up first: fewer roundings at the size of the whole sum)
 #pragma unroll
-            for (int r = 0; r < SB::R; ++r)
-#pragma unroll
-                for (int k = 0; k < VEC; ++k) bsum[k] += as_f32<E>(xb[r].v[k]);
+            for (int k = 0; k < VEC; ++k) {
+                float t = as_f32<E>(xb[0].v[k]) + as_f32<E>(xb[1].v[k]);
+                if constexpr (SB::R == 4) t += as_f32<E>(xb[2].v[k]) + as_f32<E>(xb[3].v[k]);
+                bsum[k] += t;
+            }
         }
     };
     // operand addresses: features wj + 32x + li (A), wi + 32y + li (B), unit 2 ks + kg
@@ -399,7 +402,7 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
         }
     }
     if (do_bias) {
-        // a feature's row groups, added in order
+        // a feature's row groups, added in pairs
         float *bred = reinterpret_cast<float *>(sh.stage);    // [RG][BN]
         constexpr int RG = BK / SB::R;
         static_assert(RG * C::BN * 4 <= 2 * C::STAGE, "bias scratch");
@@ -409,10 +412,14 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
             if (sb.w[k] != SB::SPARE) bred[(sb.t / SB::R) * C::BN + sb.f + k - i0] = bsum[k];
         lds_barrier();
         if (tid < C::BN && i0 + tid < Do) {
-            float s = 0.0f;
+            float p[RG];
 #pragma unroll
-            for (int r = 0; r < RG; ++r) s += bred[r * C::BN + tid];
-            s *= scale;
+            for (int r = 0; r < RG; ++r) p[r] = bred[r * C::BN + tid];
+#pragma unroll
+            for (int n = RG / 2; n >= 1; n /= 2)
+#pragma unroll
+                for (int r = 0; r < n; ++r) p[r] += p[r + n];
+            const float s = scale * p[0];
             gb[n * dout + i0 + tid] = s;
             sq += s * s;
         }

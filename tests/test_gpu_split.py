@@ -109,6 +109,20 @@ def test_linear_small_magnitudes():
     assert (abs(gW - ref) <= (T + 8) * 2.0 ** -24 * mag + 2.0 ** -140).all()
 
 
+def test_linear_bias_error():
+    """The bias gradient adds a stage's rows up before they join its sum.  A rounding is 0.42 * 2^-24 (rms) of
+    its partial sum.  Over T = 256, the squares of a thread's 8 partial sums (4.4 of the whole's), a stage's 4 rows
+    in pairs (2) and 8 row groups in pairs (3) give 0.42 * 2^-24 * sqrt(9.4) = 0.8e-7; a quarter more is
+    allowed.  (Row after row, 32 of a thread and then 8 groups, gives 1.1e-7.)"""
+    N, T, di, do = 64, 256, 100, 400
+    say("linear bias error")
+    g = torch.Generator().manual_seed(19)
+    A, B = torch.randn(N, T, di, generator=g), torch.randn(N, T, do, generator=g)
+    _, gb, _ = linear(A, B, 0, scale=1.0)
+    ref = B.double().numpy().sum(1)
+    assert np.linalg.norm(gb - ref) <= 0.97e-7 * np.linalg.norm(ref)
+
+
 def small_feature_scales(n, e):
     """2^e for every second feature, 1 for the others."""
     return torch.where(torch.arange(n) % 2 == 1, 2.0 ** e, 1.0).double()
