@@ -441,28 +441,43 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const T *__rest
             // An infinity, a NaN or a value too large to split among the inputs,
             // or outputs whose squares pass fp32's range: the wave's outputs
             // again (the stores above are done: the barrier waits for them),
-            // as plain fp32 sums.
+            // on fp32 MFMA, positions 2q + l / 32 of a step straight from memory
+            // (512 samples, 64 -> 128 @16^2, all with a NaN 1100 us; by one fma
+            // per lane and position 17100).
             if (bad) {
+                constexpr int U = 8;
+                const int c = ci0 + 32 * wi + el;
+                const T *xc = Xn + (c < s.Cin ? c : 0) * s.H * s.W, *yo = Gn + (co < s.Cout ? co : 0) * s.L;
                 gsq = 0.0f;
-                for (int e = ln; e < 1024 * (kT + 2); e += kWave) {
-                    const int x = e >> 10, c = ci0 + 32 * wi + (e & 31), o = co0 + 32 * wo + ((e >> 5) & 31);
-                    const int u = u0 + (x % kT == 0 ? row[0] : x % kT == 1 ? row[1] : row[2]), v = x < kT ? vm : vs;
+#pragma unroll 1
+                for (int x = 0; x < kT + 2; ++x) {
                     if (!(x == 0 ? on[0] : x == 1 ? on[1] : x == 2 ? on[2] : x == 3 ? on[3] : on[4])) continue;
-                    if (c >= s.Cin || o >= s.Cout) continue;
-                    float t = 0.0f;
-                    for (int oh = 0; oh < s.Ho; ++oh) {
-                        const int ih = oh * s.sh + u - s.ph;
-                        if (ih < 0 || ih >= s.H) continue;
-                        for (int ow = 0; ow < s.Wo; ++ow) {
-                            const int iw = ow * s.sw + v - s.pw;
-                            if (iw >= 0 && iw < s.W)
-                                t = fmaf(as_f32<T>(Gn[(o * s.Ho + oh) * s.Wo + ow]),
-                                         as_f32<T>(Xn[(c * s.H + ih) * s.W + iw]), t);
+                    const int u = u0 + (x % kT == 0 ? row[0] : x % kT == 1 ? row[1] : row[2]), v = x < kT ? vm : vs;
+                    f32x16_t d;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) d[r] = 0.0f;
+                    for (int p0 = 0; p0 < s.L; p0 += 2 * U) {
+                        float a[U], b[U];
+#pragma unroll
+                        for (int q = 0; q < U; ++q) {
+                            const int p = p0 + 2 * q + eg, oh = (int)((uint32_t)p / (uint32_t)s.Wo);
+                            const int ih = oh * s.sh + u - s.ph, iw = (p - oh * s.Wo) * s.sw + v - s.pw;
+                            // a position outside the input is no term of the sum
+                            const bool in = p < s.L && (uint32_t)ih < (uint32_t)s.H && (uint32_t)iw < (uint32_t)s.W;
+                            a[q] = in && c < s.Cin ? as_f32<T>(xc[ih * s.W + iw]) : 0.0f;
+                            b[q] = in && co < s.Cout ? as_f32<T>(yo[p]) : 0.0f;
                         }
+#pragma unroll
+                        for (int q = 0; q < U; ++q) d = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], d, 0, 0, 0);
                     }
-                    t *= scale;
-                    G[((i64)o * s.Cin + c) * s.khw + u * s.kw + v] = t;
-                    gsq += t * t;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int ch = cib + 8 * (r >> 2) + (r & 3);
+                        if (co >= s.Cout || ch >= s.Cin) continue;
+                        const float g = scale * d[r];
+                        G[((i64)co * s.Cin + ch) * s.khw + u * s.kw + v] = g;
+                        gsq += g * g;
+                    }
                 }
             }
         }

@@ -343,35 +343,72 @@ __device__ __forceinline__ void tile_body(const typename C::elem *__restrict__ A
     // block (x, y), register r of lane l: j = j0 + wj + 32x + 8 (r / 4) + 4 (l / 32) + r % 4, i = i0 + wi + 32y + l % 32
     const int Di = (int)din, Do = (int)dout;
     float sq = 0.0f;
-#pragma unroll
-    for (int x = 0; x < FM; ++x)
-#pragma unroll
-        for (int y = 0; y < FN; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = j0 + wj + 32 * x + 8 * (r >> 2) + 4 * kg + (r & 3), i = i0 + wi + 32 * y + li;
-                const float g = scale * (NP == 3 ? split::kUnscale * (big[x][y][r] + rest[x][y][r]) : big[x][y][r]);
-                big[x][y][r] = g;
-                const float v = i < Do && j < Di ? g : 0.0f;
-                sq += v * v;
-            }
-    float *G = gW + n * dout * din;
-    lds_barrier();                                       // the stages' LDS is free
-    if (NP == 3 && __any(!finite_f32(sq))) [[unlikely]] {
-        // An infinity, a NaN or a value too large to split among the wave's
-        // inputs, or outputs whose squares pass fp32's range: plain fp32 sums
-        // in ascending t.
+    auto finish = [&](float factor) {                    // the gradients, and their squares inside the layer
         sq = 0.0f;
-        for (int e = lane; e < 32 * FM * 32 * FN; e += kWave) {
-            const int j = j0 + wj + e % (32 * FM), i = i0 + wi + e / (32 * FM);
-            if (j >= Di || i >= Do) continue;
-            float s = 0.0f;
-            for (int t = 0; t < Ti; ++t) s = fmaf(as_f32<E>(An[t * din + j]), as_f32<E>(Bn[t * dout + i]), s);
-            s *= scale;
-            G[i * din + j] = s;
-            sq += s * s;
+#pragma unroll
+        for (int x = 0; x < FM; ++x)
+#pragma unroll
+            for (int y = 0; y < FN; ++y)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int j = j0 + wj + 32 * x + 8 * (r >> 2) + 4 * kg + (r & 3), i = i0 + wi + 32 * y + li;
+                    const float g = scale * (factor * big[x][y][r]);
+                    big[x][y][r] = g;
+                    const float v = i < Do && j < Di ? g : 0.0f;
+                    sq += v * v;
+                }
+    };
+    if constexpr (NP == 3) {
+#pragma unroll
+        for (int x = 0; x < FM; ++x)
+#pragma unroll
+            for (int y = 0; y < FN; ++y) big[x][y] += rest[x][y];
+        finish(split::kUnscale);
+        if (__any(!finite_f32(sq))) [[unlikely]] {
+            // An infinity, a NaN or a value too large to split among the wave's
+            // inputs, or outputs whose squares pass fp32's range: the wave's
+            // block again on fp32 MFMA, positions 2p + l / 32 of a step
+            // straight from memory (64 samples of 100 -> 400, T = 256, all
+            // with a NaN 54 us; by one fma per lane and position 1360).
+            constexpr int U = 8;
+#pragma unroll
+            for (int x = 0; x < FM; ++x)
+#pragma unroll
+                for (int y = 0; y < FN; ++y)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) big[x][y][r] = 0.0f;
+            for (int t0 = 0; t0 < Ti; t0 += 2 * U) {
+                float a[FM][U], b[FN][U];
+#pragma unroll
+                for (int p = 0; p < U; ++p) {
+                    const int t = t0 + 2 * p + kg;
+#pragma unroll
+                    for (int x = 0; x < FM; ++x) {
+                        const int j = j0 + wj + 32 * x + li;
+                        a[x][p] = t < Ti && j < Di ? as_f32<E>(An[t * din + j]) : 0.0f;
+                    }
+#pragma unroll
+                    for (int y = 0; y < FN; ++y) {
+                        const int i = i0 + wi + 32 * y + li;
+                        b[y][p] = t < Ti && i < Do ? as_f32<E>(Bn[t * dout + i]) : 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < U; ++p)
+#pragma unroll
+                    for (int x = 0; x < FM; ++x)
+#pragma unroll
+                        for (int y = 0; y < FN; ++y)
+                            big[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x][p], b[y][p], big[x][y], 0, 0, 0);
+            }
+            finish(1.0f);
         }
     } else {
+        finish(1.0f);
+    }
+    float *G = gW + n * dout * din;
+    lds_barrier();                                       // the stages' LDS is free
+    {
         // Through LDS, so that a wave's stores cover whole rows of its block:
         // straight from the accumulators every store instruction would touch
         // 32 rows with 32 bytes each.

@@ -261,3 +261,96 @@ def test_conv_non_finite(value):
     ok = np.isfinite(ref)
     assert (abs(gW[ok] - ref[ok]) <= 1e-5 * (abs(ref[ok]) + 1.0)).all() or value == 3.4e38
     assert np.isfinite(sq[0]) and not np.isfinite(sq[1])
+
+
+def conv_terms(X, GY, k, stride, pad):
+    """Per tap the sums over the positions inside the input alone, and the sums of their magnitudes, in 64 bits."""
+    N, ci, H, W = X.shape
+    co, ho, wo = GY.shape[1:]
+    x, y = X.double().numpy(), GY.double().numpy()
+    ref, mag = np.zeros((N, co, ci, k, k)), np.zeros((N, co, ci, k, k))
+    with np.errstate(invalid="ignore", over="ignore"):
+        for u in range(k):
+            for v in range(k):
+                rows = [o for o in range(ho) if 0 <= o * stride + u - pad < H]
+                cols = [o for o in range(wo) if 0 <= o * stride + v - pad < W]
+                a = x[:, :, [o * stride + u - pad for o in rows]][:, :, :, [o * stride + v - pad for o in cols]]
+                b = y[:, :, rows][:, :, :, cols]
+                a, b = a.reshape(N, ci, -1), b.reshape(N, co, -1)
+                ref[:, :, :, u, v] = np.einsum("nop,ncp->noc", b, a)
+                mag[:, :, :, u, v] = np.einsum("nop,ncp->noc", abs(b), abs(a))
+    return ref.reshape(N, co, -1), mag.reshape(N, co, -1)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3e38])
+@pytest.mark.parametrize("dtype,case", [("f32", (2, 40, 36, 14, 13, 3, 1, 1)), ("f32", (1, 33, 64, 21, 22, 3, 2, 1)),
+                                        ("bf16", (2, 40, 36, 14, 13, 3, 1, 0)), ("bf16", (2, 24, 40, 32, 32, 5, 2, 2)),
+                                        ("bf16", (1, 64, 33, 15, 15, 4, 1, 2))],
+                         ids=lambda c: c if isinstance(c, str) else "x".join(map(str, c)))
+def test_conv_sums_again(dtype, case, value):
+    """Values that the bf16 sums cannot take reach exactly the outputs they reach in plain fp32 sums, and all
+    other outputs keep the bound."""
+    N, ci, co, H, W, k, st, pad = case
+    say("conv sums again", dtype, case, value)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(20)
+    ho, wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    X = torch.randn(N, ci, H, W, generator=g).to(td)
+    GY = (torch.randn(N, co, ho, wo, generator=g) / 1000).to(td)
+    X[0, ci - 1, 0, W - 1] = X[0, 3, H // 2, 0] = value      # a corner and an edge: only some taps reach them
+    GY[0, 5] = 0.0
+    gW, gb, sq = conv(X, GY, k, st, pad, 0, 1.0)
+    ref, mag = conv_terms(X, GY, k, st, pad)
+    np.testing.assert_array_equal(np.isnan(gW), np.isnan(ref))
+    np.testing.assert_array_equal(np.isinf(gW), np.isinf(ref))
+    ok = np.isfinite(ref)
+    assert (gW[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+    assert (abs(gW[ok] - ref[ok]) <= (ho * wo + 8) * 2.0 ** -24 * mag[ok]).all()
+    assert np.isfinite(sq[1:]).all() and not np.isfinite(sq[0])
+
+
+@pytest.mark.parametrize("kind", ["linear", "conv", "conv_bf16"])
+def test_non_finite_cost(kind):
+    """A batch with non-finite samples takes the fp32 matrix units, not one multiply-add per lane and position:
+    a pass over memory and MFMAs of a sixteenth of the rate, so some ten times the ordinary pass at most."""
+    say("non-finite cost", kind)
+    dt = dp.DP_BF16 if kind == "conv_bf16" else dp.DP_F32
+    td = torch.bfloat16 if dt == dp.DP_BF16 else torch.float32
+    if kind == "linear":
+        N, T, di, do = 64, 256, 100, 400
+        a, b = torch.randn(N, T, di, device=DEV), torch.randn(N, T, do, device=DEV)
+        gW, gb = torch.empty(N, do, di, device=DEV), torch.empty(N, do, device=DEV)
+        ws = torch.empty(dp.dp_grad_sample_linear_workspace_bytes(N, T, di, do, dt), dtype=torch.uint8, device=DEV)
+    else:
+        N, ci, co, H = 256, 64, 128, 16
+        a, b = torch.randn(N, ci, H, H, device=DEV).to(td), torch.randn(N, co, H, H, device=DEV).to(td)
+        gW, gb = torch.empty(N, co, ci * 9, device=DEV), torch.empty(N, co, device=DEV)
+        geom = (3, 3, 1, 1, 1, 1)
+        ws = torch.empty(max(dp.dp_grad_sample_conv2d_workspace_bytes(N, ci, H, H, co, *geom), 4), dtype=torch.uint8,
+                         device=DEV)
+    sq = torch.empty(N, device=DEV)
+
+    def call():
+        if kind == "linear":
+            dp.dp_grad_sample_linear(a, b, dt, N, T, di, do, 1.0, gW, gb, sq, None, ws)
+        else:
+            dp.dp_grad_sample_conv2d(a, b, dt, N, ci, H, H, co, H, H, *geom, 1, 1, 1, 1.0, gW, gb, sq, None, ws)
+
+    def us():
+        best = 1e9
+        for _ in range(5):
+            s, e = torch.cuda.Event(True), torch.cuda.Event(True)
+            s.record()
+            for _ in range(5):
+                call()
+            e.record()
+            torch.cuda.synchronize()
+            best = min(best, s.elapsed_time(e) * 200)
+        return best
+
+    call()
+    ordinary = us()
+    a.view(N, -1)[:, 77] = float("nan")
+    worst = us()
+    print("[case] ordinary %.1f us, every sample with a NaN %.1f us" % (ordinary, worst), file=sys.stderr, flush=True)
+    assert worst <= 20 * ordinary
