@@ -657,16 +657,41 @@ int conv_path()
 }
 }  // namespace dpg
 
-// Whether the automatic choice runs the row chunks on the bf16 matrix units:
-// instead of the fp32 row-chunked kernel, and, for wide rows that that kernel's
-// stage does not hold, instead of the tiled one (64 samples, 64 -> 64 channels,
-// 56 x 56: 865 us there) where the fp32 rule says so, which then holds for both
-// types (dp_conv2d_kernel_choice does not know the type).
-static bool split_chosen(const ConvRowsArgs &rows, bool bf, int slots)
+// The tiled kernel's time in us (fitted to 340 drawn layers, 15% rms): per
+// round of the workgroups that a CU holds a start, the chunks, the planes staged
+// and the positions, with a wave's share of the MFMAs; gathered through the
+// cache where the planes do not fit LDS.
+static double conv_tiled_us(const ConvRowsArgs &a)
+{
+    const ConvShape s = make_shape(a.Cin, a.H, a.W, a.Cout, a.kh, a.kw, a.sh, a.sw, a.ph, a.pw);
+    const Plan p = plan_conv(s, (long)a.N);
+    const double grid = (double)a.N * conv_tiles(s, (long)a.N);
+    const auto up = [](double x, double y) { return (double)(i64)((x + y - 1) / y); };
+    if (p.cfg < 0) return 4.0 + 0.137 * s.L * (0.5 + 0.5 * up(grid, 256));
+    const CfgDesc &c = kConfigs[p.cfg];
+    int held = (int)(163840 / (p.lds + 4096));
+    if (held > 2048 / threads_of(c)) held = 2048 / threads_of(c);
+    if (held < 1) held = 1;
+    const double whole = (double)(i64)(grid / (256.0 * held)), left = grid - whole * 256.0 * held;
+    const double rounds = whole + (left > 0 ? 0.5 + 0.5 * up(left, 256) / held : 0.0);
+    const double mfmas = (double)c.FM * c.FN / c.WK;
+    return 5.0 + rounds * (8.8 + 1.3 * up(s.L, p.g.bk) + 0.00018 * p.g.nplanes * p.g.plane + s.L * (0.0125 + 0.06 * mfmas));
+}
+
+// Whether the automatic choice runs the row chunks on the bf16 matrix units,
+// instead of the fp32 row-chunked kernel or, for rows that that kernel's stage
+// does not hold, the tiled one.  Their times are compared, as few workgroups
+// of long chains lose to many short ones whatever the rates: 6 samples 184 -> 26
+// @36x57 fp32 82 us tiled against 263, 12 samples 42 -> 11 @13x63 34 against
+// 119, 149 samples 116 -> 31 @7x8 5x5 bf16 34 by rows against 96, but 33
+// samples 93 -> 10 @56^2 fp32 586 tiled against 235.  Of 3000 drawn layers the
+// sizes alone made 134 over 5% slower than those kernels (up to 4.8 times), the
+// times 34 (up to 1.5 times, fp32 1.2); 29 lose a gain (up to 1.6 times).
+static bool split_chosen(const ConvRowsArgs &a, bool bf, int slots)
 {
     if (g_conv_path != DP_CONV_AUTO) return false;
-    if (conv_rows_preferred(rows)) return conv_split_ok(rows, bf, slots);
-    return conv_split_ok(rows, false, slots) && conv_split_ok(rows, true, slots);
+    const double us = conv_split_us(a, bf, slots);
+    return us > 0.0 && us < 0.95 * (conv_rows_preferred(a) ? conv_rows_us(a) : conv_tiled_us(a));
 }
 
 extern "C" int dp_conv2d_set_path(int path)

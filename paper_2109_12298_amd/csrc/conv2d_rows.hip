@@ -689,19 +689,34 @@ int conv_rows_tiles(const ConvRowsArgs &a)
     return s.ktiles * s.ctiles;
 }
 
+// 16-byte runs (8-byte for bf16) where rows and pointers allow; three
+// workgroups per CU where their smaller stage still takes chunks of four
+// or more output rows (or the whole plane)
+static int choose_variant(const ConvRowsArgs &a, bool runs, RowsShape &s)
+{
+    if (runs && plan_rows(a, kSmall4, s) && (s.RC >= 4 || s.RC == s.Ho)) return 1;
+    if (runs && plan_rows(a, kLarge4, s)) return 0;
+    return plan_rows(a, kSingle, s) ? 2 : -1;
+}
+
+double conv_rows_us(const ConvRowsArgs &a)
+{
+    RowsShape s;
+    const int which = choose_variant(a, true, s);
+    if (which < 0) return 0.0;
+    const double pc = (double)s.RC * s.Wo, bn = s.Cout > 32 ? 64 : 32, chunks = (s.Ho + s.RC - 1) / s.RC;
+    const double stage = ((double)s.np * s.XR * s.W + pc * bn) / 1000.0, mfmas = pc * s.nblk * bn / 32;
+    const double store = s.KK % 4 ? 0.016 * s.nblk * bn : 0.0;
+    const double chunk = 1.7 + mfmas * (s.fast ? 0.005 : 0.0075) + stage * (which == 2 ? 0.79 : 0.22) + 0.022 * pc;
+    return 5.2 + cu_rounds((double)a.N * s.ktiles * s.ctiles, which == 1 ? 3 : 2, 0.8) * (2.8 + store + chunks * chunk);
+}
+
 void conv_rows_launch(const ConvRowsArgs &a, bool bf16, float scale, float *gW, float *gb, float *sqnorm,
                       float *partial, hipStream_t stream)
 {
-    // 16-byte runs (8-byte for bf16) where rows and pointers allow; three
-    // workgroups per CU where their smaller stage still takes chunks of four
-    // or more output rows (or the whole plane)
     RowsShape s;
     const int run_bytes = 4 * (bf16 ? 2 : 4);
-    const bool runs = aligned(a.X, run_bytes) && aligned(a.GY, run_bytes);
-    int which = 2;
-    if (runs && plan_rows(a, kSmall4, s) && (s.RC >= 4 || s.RC == s.Ho)) which = 1;
-    else if (runs && plan_rows(a, kLarge4, s)) which = 0;
-    else plan_rows(a, kSingle, s);
+    const int which = choose_variant(a, aligned(a.X, run_bytes) && aligned(a.GY, run_bytes), s);
     s.vec = s.KK % 4 == 0 && aligned(gW, 16);
     const int tiles = s.ktiles * s.ctiles;
     const int direct = tiles == 1;

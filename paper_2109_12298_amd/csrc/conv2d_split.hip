@@ -569,8 +569,8 @@ ConvGeom geom(const ConvRowsArgs &a)
 }  // namespace
 
 // Measured against the row-chunked fp32 MFMA kernel (us, that one / this one).
-// What decides is the positions a workgroup contracts per output it stores,
-// so the rule is on useful = positions x the filled part of the channel blocks.
+// What decides for a full chip is the positions a workgroup contracts per output it stores,
+// so the first rule is on useful = positions x the filled part of the channel blocks.
 // fp32, 3 x 3 at stride 1, useful >= 96: 512 samples 32 -> 64 @32^2 192 / 130,
 // 64 -> 128 @16^2 223 / 160, 256 samples 64 -> 64 @12^2 41 / 37, 128 samples
 // 24 -> 48 @30^2 173 / 79; below: 512 samples 128 -> 256 @8^2 (useful 64)
@@ -584,18 +584,21 @@ ConvGeom geom(const ConvRowsArgs &a)
 // 59 / 35, 512 samples 64 -> 128 @16^2 221 / 120, 300 samples 100 -> 24 @9^2
 // 53 / 35, 50 samples 40 -> 40 @13^2 5 x 5 41 / 32; below: 200 samples
 // 64 -> 30 @6^2 17 / 19, 64 samples 24 -> 24 @20^2 7 x 7 stride 2 24 / 33.
-bool conv_split_ok(const ConvRowsArgs &a, bool bf16, int slots)
+double conv_split_us(const ConvRowsArgs &a, bool bf16, int slots)
 {
-    if (a.Cin < 24 || a.kh * a.kw < 2 || a.N * slots >= (i64(1) << 31)) return false;
+    if (a.Cin < 24 || a.kh * a.kw < 2 || a.N * slots >= (i64(1) << 31)) return 0.0;
     const double fill = (double)(a.Cin * a.Cout) / (double)(ceil_div(a.Cin, 32) * ceil_div(a.Cout, 32) * 1024);
     const double useful = (double)(a.Ho * a.Wo) * fill;
+    if (useful < 40.0) return 0.0;
+    if (!bf16) {
+        if (a.kh != 3 || a.kw != 3) return 0.0;
+        if (a.sh == 1 && a.sw == 1 ? useful < 96.0 : useful < 64.0 || a.N * conv_rows_tiles(a) >= 256) return 0.0;
+    }
     SplitShape s;
     int which;
-    if (useful < 40.0 || !choose(geom(a), bf16, slots, s, which)) return false;
-    if (bf16) return useful >= (s.ngrp > 4 ? 90.0 : 40.0);
-    if (a.kh != 3 || a.kw != 3) return false;
-    if (a.sh == 1 && a.sw == 1) return useful >= 96.0;
-    return useful >= 64.0 && a.N * conv_rows_tiles(a) < 256;
+    if (!choose(geom(a), bf16, slots, s, which) || (bf16 && s.ngrp > 4 && useful < 90.0)) return 0.0;
+    return split_us(s, kLayouts[which], bf16, cu_rounds((double)a.N * s.tiles, 2, 0.85),
+                    (double)ceil_div(a.N * s.tiles, 256));
 }
 
 void conv_split_launch(const ConvRowsArgs &a, bool bf16, int slots, float scale, float *gW, float *gb, float *sqnorm,
@@ -603,7 +606,7 @@ void conv_split_launch(const ConvRowsArgs &a, bool bf16, int slots, float scale,
 {
     SplitShape s;
     int which;
-    if (!choose(geom(a), bf16, slots, s, which)) return;      // conv_split_ok said yes
+    if (!choose(geom(a), bf16, slots, s, which)) return;      // conv_split_us took it
     const bool direct = s.tiles == 1;
     s.full = s.full == 2 ? 1 : 0;
     float *sqout = sqnorm ? (direct ? sqnorm : partial) : nullptr;

@@ -7,10 +7,11 @@
 
 namespace dpg {
 
-// Whether the kernel takes the shape and is the better choice for it.
+// The kernel's time in us, 0 where it does not take the shape or has measured
+// slower whatever the grid (the caller compares it with the kernel it would replace).
 // slots: squared-norm partials per sample that the call's workspace holds
 // (1: no workspace, one tile per sample).
-bool conv_split_ok(const ConvRowsArgs &a, bool bf16, int slots);
+double conv_split_us(const ConvRowsArgs &a, bool bf16, int slots);
 void conv_split_launch(const ConvRowsArgs &a, bool bf16, int slots, float scale, float *gW, float *gb, float *sqnorm,
                        float *partial, hipStream_t stream);
 

@@ -172,6 +172,24 @@ inline double cost_of(const SplitShape &s, const Layout &w, int64_t N, bool bf16
     return (c / groups + 8000.0) * (rounds > 1.0 ? rounds : 1.0);
 }
 
+// A plan's time in us, for comparison with the kernels it may replace; rounds:
+// of its grid over the CUs (cu_rounds), per CU: workgroups one after the other.
+// Fitted to 3300 drawn layers (the largest stay within 1.3 times, 8% rms for
+// fp32 and 14% for bf16): a fixed part, the stores (single words of every tap
+// per lane, each its own cache line, unless whole rows of 3 x 3 taps go through LDS), and per chunk the
+// round trips of its loads (two units per thread each), its units, and its
+// steps with their MFMAs.
+inline double split_us(const SplitShape &s, const Layout &w, bool bf16, double rounds, double per_cu)
+{
+    const int chunks = (s.Ho + s.RC - 1) / s.RC, steps = ((s.RC * s.NU + 1) / 2 + w.wk - 1) / w.wk;
+    const int trips = (s.nx + 511) / 512 + (s.ng + 511) / 512, units = (s.nx + 255) / 256 + (s.ng + 255) / 256;
+    const double taps = (double)s.khw / s.ngrp, blocks = w.wi * w.wo;
+    const double store = s.full == 2 ? (bf16 ? 2.2 : 2.1) : (bf16 ? 0.51 : 0.49) * s.gpw * taps;
+    const double chunk = bf16 ? 1.8 + 0.78 * trips + 0.076 * units + 0.0085 * steps * (taps + 8)
+                              : 0.5 + 1.8 * trips + 0.16 * units + 0.012 * steps * (6 * taps + 8);
+    return (bf16 ? 9.5 : 11.6) + per_cu * blocks * store + rounds * s.gpw * chunks * chunk;
+}
+
 inline bool choose(const ConvGeom &a, bool bf16, int slots, SplitShape &best, int &which)
 {
     // 32-bit offsets, taps in eight bits, and the quotients of inv_nu and div20

@@ -217,21 +217,26 @@ def test_linear_large_values(value):
     assert np.isfinite(sq).all()
 
 
-# N, Cin, Cout, H, W, k, stride, pad: the shapes the automatic choice gives the
+# N, Cin, Cout, H, W, k, stride, pad: shapes that the automatic choice gives the
 # bf16-matrix kernel, at the edges of its channel blocks (32, 64), units of
 # eight columns, row chunks, tap groups and shifts
 CONVS = [
-    (2, 32, 64, 16, 16, 3, 1, 1), (3, 24, 33, 15, 17, 3, 1, 1), (1, 65, 40, 13, 24, 3, 1, 0), (2, 33, 31, 20, 9, 3, 1, 2),
-    (1, 64, 64, 12, 63, 3, 1, 1), (2, 40, 130, 11, 11, 3, 1, 1), (1, 31, 64, 33, 40, 3, 2, 1), (2, 64, 64, 18, 23, 3, 2, 0),
-    (1, 24, 32, 28, 30, 3, 1, 1), (300, 32, 64, 12, 12, 3, 1, 1), (2, 25, 70, 10, 57, 3, 1, 1),
+    (2, 32, 64, 16, 16, 3, 1, 1), (3, 24, 33, 15, 17, 3, 1, 1), (1, 65, 40, 13, 24, 3, 1, 0), (1, 33, 64, 20, 9, 3, 1, 2),
+    (1, 25, 10, 56, 56, 3, 1, 1), (2, 40, 130, 13, 16, 3, 1, 1), (1, 31, 64, 33, 40, 3, 2, 1), (2, 64, 64, 18, 23, 3, 2, 0),
+    (1, 24, 32, 28, 30, 3, 1, 1), (1, 25, 10, 56, 63, 3, 1, 1), (1, 33, 64, 20, 24, 3, 1, 2),
 ]
 CONVS_BF16 = CONVS + [
-    (3, 24, 40, 27, 27, 5, 2, 2), (2, 40, 24, 13, 14, 5, 1, 0), (1, 24, 24, 19, 21, 7, 1, 3), (2, 26, 33, 21, 26, 4, 2, 1),
-    (1, 30, 64, 14, 15, 2, 1, 0), (2, 64, 32, 9, 9, 3, 3, 1),
+    (3, 24, 40, 27, 27, 5, 2, 2), (2, 40, 24, 17, 18, 5, 1, 0), (1, 24, 24, 19, 21, 7, 1, 3), (2, 26, 33, 21, 26, 4, 2, 1),
+    (1, 30, 64, 14, 15, 2, 1, 0), (2, 64, 32, 25, 25, 3, 3, 1), (1, 32, 32, 32, 32, 9, 2, 4),
     # several tap groups, with rows of GY that fill their units exactly
-    (2, 24, 40, 32, 32, 5, 2, 2), (2, 24, 40, 31, 31, 5, 2, 2), (2, 32, 64, 16, 16, 5, 2, 2), (2, 32, 64, 16, 16, 4, 2, 1),
-    (2, 32, 64, 32, 32, 4, 2, 1), (1, 64, 64, 32, 32, 7, 2, 3), (2, 32, 64, 15, 15, 4, 1, 2), (2, 32, 64, 14, 14, 5, 1, 3),
-    (2, 32, 64, 24, 24, 5, 3, 1),
+    (2, 24, 40, 32, 32, 5, 2, 2), (2, 24, 40, 31, 31, 5, 2, 2), (2, 32, 64, 32, 32, 4, 2, 1), (1, 64, 64, 32, 32, 7, 2, 3),
+    (2, 32, 64, 15, 15, 4, 1, 2), (2, 32, 64, 14, 14, 5, 1, 3), (1, 32, 64, 48, 48, 5, 3, 1), (1, 32, 32, 13, 13, 6, 1, 4),
+]
+# shapes on the other side of that choice, by their grid or their size
+CONVS_OTHER = [
+    (2, 33, 31, 20, 9, 3, 1, 2), (1, 64, 64, 12, 63, 3, 1, 1), (2, 40, 130, 11, 11, 3, 1, 1), (300, 32, 64, 12, 12, 3, 1, 1),
+    (2, 25, 70, 10, 57, 3, 1, 1), (2, 40, 24, 13, 14, 5, 1, 0), (2, 64, 32, 9, 9, 3, 3, 1), (2, 32, 64, 16, 16, 5, 2, 2),
+    (2, 32, 64, 16, 16, 4, 2, 1), (2, 32, 64, 24, 24, 5, 3, 1), (6, 27, 5, 37, 63, 3, 1, 1), (3, 116, 31, 7, 8, 5, 1, 2),
 ]
 
 
@@ -261,13 +266,9 @@ def conv_reference(X, GY, k, stride, pad, scale=1.5):
     return scale * torch.bmm(y, u).numpy(), scale * torch.bmm(y.abs(), u.abs()).numpy(), scale * y.sum(2).numpy()
 
 
-@pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("dtype,case", [("f32", c) for c in CONVS] + [("bf16", c) for c in CONVS_BF16],
-                         ids=lambda c: c if isinstance(c, str) else "x".join(map(str, c)))
-def test_conv_edges(dtype, case, shift):
+def check_conv(dtype, case, shift):
     N, ci, co, H, W, k, st, pad = case
     say("conv", case, dtype, "shift", shift)
-    assert dp.dp_conv2d_kernel_choice(N, ci, H, W, co, k, k, st, st, pad, pad) == dp.DP_CONV_KERNEL_ROWS
     g = torch.Generator().manual_seed(ci * 100 + H)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
     ho, wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
@@ -280,6 +281,61 @@ def test_conv_edges(dtype, case, shift):
     assert (abs(gb - rb) <= bound * 1.5 * GY.double().abs().sum((2, 3)).numpy()).all()
     sref = (gW.astype(np.float64) ** 2).sum((1, 2)) + (gb.astype(np.float64) ** 2).sum(1)
     assert (abs(sq - sref) <= 1e-5 * sref).all()
+    return gW, X, GY
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dtype,case", [("f32", c) for c in CONVS] + [("bf16", c) for c in CONVS_BF16],
+                         ids=lambda c: c if isinstance(c, str) else "x".join(map(str, c)))
+def test_conv_edges(dtype, case, shift):
+    gW, X, GY = check_conv(dtype, case, shift)
+    # the kernel ran: sums in the order of the fp32 matrix units differ from its own somewhere
+    before = dp.dp_conv2d_set_path(dp.DP_CONV_ROWS)
+    try:
+        other = conv(X, GY, case[5], case[6], case[7], shift)[0]
+    finally:
+        dp.dp_conv2d_set_path(before)
+    assert not np.array_equal(gW, other), "not the bf16-matrix kernel"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CONVS_OTHER, ids=lambda c: "x".join(map(str, c)))
+def test_conv_other_side_of_the_choice(dtype, case):
+    check_conv(dtype, case, 0)
+
+
+@pytest.mark.parametrize("dtype,case", [("f32", (6, 184, 26, 36, 57, 3, 1, 1)), ("f32", (12, 42, 11, 13, 63, 3, 1, 1)),
+                                        ("f32", (9, 32, 69, 19, 45, 3, 3, 1)), ("bf16", (149, 116, 31, 7, 8, 5, 1, 2)),
+                                        ("bf16", (98, 160, 89, 8, 8, 5, 1, 2))],
+                         ids=lambda c: c if isinstance(c, str) else "x".join(map(str, c)))
+def test_conv_choice_is_not_the_slower_kernel(dtype, case):
+    """Layers that the bf16-matrix kernel takes two to four times as long for: the choice is within a third of
+    the best kernel that can be forced."""
+    N, ci, co, H, W, k, st, pad = case
+    say("conv choice", dtype, case)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ho, wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    X, GY = torch.randn(N, ci, H, W, device=DEV).to(td), torch.randn(N, co, ho, wo, device=DEV).to(td)
+    gW, gb, sq = torch.empty(N, co, ci * k * k, device=DEV), torch.empty(N, co, device=DEV), torch.empty(N, device=DEV)
+    geom = (k, k, st, st, pad, pad)
+    ws = torch.empty(max(dp.dp_grad_sample_conv2d_workspace_bytes(N, ci, H, W, co, *geom), 4), dtype=torch.uint8, device=DEV)
+    times = {}
+    for path in (dp.DP_CONV_TILED, dp.DP_CONV_ROWS, dp.DP_CONV_AUTO):
+        before = dp.dp_conv2d_set_path(path)
+        try:
+            for _ in range(4):
+                s, e = torch.cuda.Event(True), torch.cuda.Event(True)
+                s.record()
+                for _ in range(10):
+                    dp.dp_grad_sample_conv2d(X, GY, dp.dtype_of(X), N, ci, H, W, co, ho, wo, *geom, 1, 1, 1, 1.0, gW, gb,
+                                             sq, None, ws)
+                e.record()
+                torch.cuda.synchronize()
+                times[path] = min(times.get(path, 1e9), s.elapsed_time(e) * 100)
+        finally:
+            dp.dp_conv2d_set_path(before)
+    print("[case] us", times, file=sys.stderr, flush=True)
+    assert times[dp.DP_CONV_AUTO] <= 1.33 * min(times.values())
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
