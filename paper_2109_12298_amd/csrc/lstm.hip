@@ -136,7 +136,7 @@ __global__ __launch_bounds__(UP > 4 ? 256 : 512) void lstm_bptt_kernel(const flo
     typedef std::integral_constant<int, 0x4E> Xor2;
     typedef std::integral_constant<int, 0x128> Ror8;         // lane i of 16 <-> i + 8
 
-    float dc_f = 0.0f;              // dc_{t+1} f_{t+1}
+    float dc_next = 0.0f, f_next = 0.0f;        // dc_{t+1} and f_{t+1}
     int cur = 0;
     auto step = [&](int t, const float (&v)[NV], float cp) {
         const float *d = dbuf[cur ^ 1] + 2 * k16;
@@ -198,7 +198,8 @@ __global__ __launch_bounds__(UP > 4 ? 256 : 512) void lstm_bptt_kernel(const flo
         }
         if constexpr (UP <= 4) sum += dpp(sum, Xor2());
         sum += dpp(sum, Ror8());
-        const float dh = sum + add, dc = __builtin_fmaf(dh, e, dc_f);
+        // (of the two products the chain's, dc f, is the one that is not rounded)
+        const float dh = sum + add, dc = __builtin_fmaf(dc_next, f_next, dh * e);
         if constexpr (UP > 4) {
             const float v0 = dc * fac, v1 = (q ? dh : dc) * fac2;
             if (live) {
@@ -215,7 +216,8 @@ __global__ __launch_bounds__(UP > 4 ? 256 : 512) void lstm_bptt_kernel(const flo
                 dn[(i64)t * G + q * H + u] = val;
             }
         }
-        dc_f = dc * gf;
+        dc_next = dc;
+        f_next = gf;
         lds_barrier();
         cur ^= 1;
     };
