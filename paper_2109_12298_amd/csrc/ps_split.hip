@@ -721,8 +721,9 @@ void launch_kind(Kind kind, const PsLayer &L, i64 N, hipStream_t stream)
 
 bool ps_split_ok(dp_dtype dt, i64 T, i64 din, i64 dout)
 {
+    // (positions up to three stages past the last one are counted in 32 bits)
     const i64 least = dt == DP_F32 ? 4 : 8, most = i64(1) << 22;
-    return T >= 2 && T < (i64(1) << 31) && din >= least && dout >= least && din < most && dout < most;
+    return T >= 2 && T < (i64(1) << 31) - 256 && din >= least && dout >= least && din < most && dout < most;
 }
 
 int ps_split_parts(i64 din, i64 dout) { return (int)tiles_of(kSmall, din, dout); }

@@ -15,7 +15,8 @@ struct PsLayer {
 };
 
 // A and B rows of at least 16 bytes (a load that would pass a row's end is
-// moved back inside it) and features below 2^22 (32-bit offsets in a stage).
+// moved back inside it), features below 2^22 (32-bit offsets in a stage) and
+// positions that 32 bits count.
 bool ps_split_ok(dp_dtype dt, i64 T, i64 din, i64 dout);
 // squared-norm partials per sample
 int ps_split_parts(i64 din, i64 dout);

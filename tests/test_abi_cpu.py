@@ -1,5 +1,6 @@
 """C-ABI contract on the CPU: the library loads, exports every declared symbol,
 and rejects invalid arguments on the host before anything reaches HIP."""
+import ctypes
 import math
 import os
 import re
@@ -340,3 +341,15 @@ def test_ghost_norm_many_validation():
     # empty batches and empty lists enqueue nothing
     assert code_of(f, items, 6, dp.DP_BF16, 0, stream=0) == dp.DP_OK
     assert code_of(f, items, 0, dp.DP_BF16, 32, stream=0) == dp.DP_OK
+
+
+def test_sequence_kernel_takes_no_more_positions_than_its_indexes_hold():
+    """The kernel counts positions in 32 bits, up to two stages of 64 past the last one."""
+    ok = getattr(dp.lib(), "_ZN3dpg11ps_split_okE8dp_dtypelll")       # dpg::ps_split_ok(dp_dtype, i64, i64, i64)
+    ok.restype = ctypes.c_bool
+    ok.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
+    top = 2 ** 31 - 1
+    for dt in (dp.DP_F32, dp.DP_BF16):
+        assert ok(dt, 2, 8, 8) and ok(dt, 2 ** 30, 8, 8)
+        taken = [T for T in list(range(top - 600, top + 1)) + [2 ** 31, 2 ** 40 - 1] if ok(dt, T, 8, 8)]
+        assert all(T + 3 * 64 <= top for T in taken)
