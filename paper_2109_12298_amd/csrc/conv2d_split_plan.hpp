@@ -38,7 +38,7 @@ struct SplitShape {
     int inv_xrow, inv_grow;            // ceil(2^20 / (XR * NU)), ceil(2^20 / (RC * gl))
     int nci, nco, ngrp, gpw, tiles;    // channel tiles, groups, groups per workgroup, workgroups per sample
     int bias_at;                       // byte offset of the bias sums (one float per GY unit of a chunk), 0: none
-    int full;                          // kh == kw == 3 in one group with stores by rows
+    bool full;                         // 3 x 3 taps in one group: stores by whole rows
     ConvGroup g[kMaxGroups];
 };
 
@@ -96,7 +96,7 @@ inline bool plan(const ConvGeom &a, bool bf16, int slots, const Layout &w, Split
     s.nco = (s.Cout + 32 * w.wo - 1) / (32 * w.wo);
     // tap groups: rows in balanced threes; columns of one phase in balanced threes
     s.ngrp = 0;
-    bool all3 = true, zero_ends = true;
+    bool zero_ends = true;
     const int nu = (s.kh + kT - 1) / kT;
     for (int i = 0; i < nu; ++i) {
         const int u0 = i * s.kh / nu, u1 = (i + 1) * s.kh / nu;
@@ -108,7 +108,6 @@ inline bool plan(const ConvGeom &a, bool bf16, int slots, const Layout &w, Split
                 const int vc = f + s.sw * (v0 + (vl == 3 ? 1 : 0));
                 const int dv = vc - s.pw, sc = dv >= 0 ? dv / s.sw : -((s.sw - 1 - dv) / s.sw);
                 s.g[s.ngrp++] = {(int8_t)u0, (int8_t)(u1 - u0), (int8_t)vc, (int8_t)vl, (int16_t)sc, (int16_t)(dv - sc * s.sw)};
-                all3 = all3 && vl == 3 && u1 - u0 == 3;
                 // GY[-1 - sc] and GY[8 NU - sc] are outside the row
                 zero_ends = zero_ends && (vl == 1 || (sc >= 0 && 8 * s.NU - sc >= s.Wo));
             }
@@ -117,7 +116,7 @@ inline bool plan(const ConvGeom &a, bool bf16, int slots, const Layout &w, Split
     s.gl = zero_ends ? s.NU : s.NU + 2;
     s.gp = zero_ends ? s.NU + 1 : s.NU + 2;
     s.inv_gl = (65536 + s.gl - 1) / s.gl;
-    s.full = all3 ? (s.kh == 3 && s.kw == 3 && s.sw == 1 ? 2 : 1) : 0;
+    s.full = s.kh == 3 && s.kw == 3 && s.sw == 1;
     const int room = slots / (s.nci * s.nco);
     if (room < 1) return false;
     s.gpw = (s.ngrp + room - 1) / room;
@@ -184,7 +183,7 @@ inline double split_us(const SplitShape &s, const Layout &w, bool bf16, double r
     const int chunks = (s.Ho + s.RC - 1) / s.RC, steps = ((s.RC * s.NU + 1) / 2 + w.wk - 1) / w.wk;
     const int trips = (s.nx + 511) / 512 + (s.ng + 511) / 512, units = (s.nx + 255) / 256 + (s.ng + 255) / 256;
     const double taps = (double)s.khw / s.ngrp, blocks = w.wi * w.wo;
-    const double store = s.full == 2 ? (bf16 ? 2.2 : 2.1) : (bf16 ? 0.51 : 0.49) * s.gpw * taps;
+    const double store = s.full ? (bf16 ? 2.2 : 2.1) : (bf16 ? 0.51 : 0.49) * s.gpw * taps;
     const double chunk = bf16 ? 1.8 + 0.78 * trips + 0.076 * units + 0.0085 * steps * (taps + 8)
                               : 0.5 + 1.8 * trips + 0.16 * units + 0.012 * steps * (6 * taps + 8);
     return (bf16 ? 9.5 : 11.6) + per_cu * blocks * store + rounds * s.gpw * chunks * chunk;
