@@ -6,8 +6,8 @@
 //   ggamma_n[c] = s * sum_p B[n][c][p] * xhat[n][c][p]
 //   gbeta_n[c]  = s * sum_p B[n][c][p]
 // over the channel's P spatial positions, which are contiguous in memory.
-// A wave reduces one channel at a time (lanes over the positions, 16-byte
-// loads at any alignment, up to four of each operand in flight, then a fixed
+// A wave reduces one channel at a time (lanes over the positions, loads of four
+// elements at any alignment, up to four of each operand in flight, then a fixed
 // tree), or, for planes of at most 64
 // positions, four channels at a time on 16 lanes each; the sums are
 // deterministic.  A workgroup takes 16 channels of one sample, and the
@@ -47,7 +47,7 @@ __device__ __forceinline__ float seg_sum(float v)
 }
 
 // LPC: lanes per channel (64, or 16 for planes of at most 64 positions);
-// kLoads: 16-byte loads of each operand in flight per lane (0: single elements)
+// kLoads: loads of four elements of each operand in flight per lane (0: single elements)
 template <typename T, int LPC, int kLoads, bool NT>
 __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict__ xh, const T *__restrict__ B,
                                                              i64 C, i64 P, int cblocks, float scale,
@@ -77,22 +77,36 @@ __global__ __launch_bounds__(kThreads) void gn_affine_kernel(const T *__restrict
             }
         }
         if (live && kLoads > 0) {
-            constexpr int L = kLoads > 0 ? kLoads : 1;
-            for (i64 p0 = 4 * sl; p0 < P4; p0 += 4 * LPC * L) {
-                float4 bv[L], xv[L];
+            constexpr int L = kLoads > 0 ? kLoads : 1, kStep = 4 * LPC * L;
+            const auto add = [&](const float4 &b4, const float4 &x4) {
+                ag += (b4.x * x4.x + b4.y * x4.y) + (b4.z * x4.z + b4.w * x4.w);
+                ab += (b4.x + b4.y) + (b4.z + b4.w);
+            };
+            float4 bv[L], xv[L];
+            i64 p0 = 4 * sl;
+            // (one load per step: each lane's own bound)
+            for (; L == 1 ? p0 < P4 : p0 + kStep <= P4 + 4 * sl; p0 += kStep) {
 #pragma unroll
-                for (int k = 0; k < L; ++k) {
-                    const i64 p = p0 + 4 * LPC * k < P4 ? p0 + 4 * LPC * k : p0;
-                    bv[k] = ld4<T, NT>(b + p);
-                    xv[k] = ld4<T, NT>(x + p);
+                for (int j = 0; j < L; ++j) {
+                    bv[j] = ld4<T, NT>(b + p0 + 4 * LPC * j);
+                    xv[j] = ld4<T, NT>(x + p0 + 4 * LPC * j);
                 }
 #pragma unroll
-                for (int k = 0; k < L; ++k) {
-                    const bool in = p0 + 4 * LPC * k < P4;
-                    const float g = (bv[k].x * xv[k].x + bv[k].y * xv[k].y) + (bv[k].z * xv[k].z + bv[k].w * xv[k].w);
-                    ag += in ? g : 0.0f;
-                    ab += in ? (bv[k].x + bv[k].y) + (bv[k].z + bv[k].w) : 0.0f;
+                for (int j = 0; j < L; ++j) add(bv[j], xv[j]);
+            }
+            // what is left of a step: only the lanes and loads inside the plane (past the caches, a load
+            // repeated to fill the step is read from memory again)
+            if (L > 1 && p0 < P4) {
+#pragma unroll
+                for (int j = 0; j < L; ++j) {
+                    bv[j] = xv[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (p0 + 4 * LPC * j < P4) {
+                        bv[j] = ld4<T, NT>(b + p0 + 4 * LPC * j);
+                        xv[j] = ld4<T, NT>(x + p0 + 4 * LPC * j);
+                    }
                 }
+#pragma unroll
+                for (int j = 0; j < L; ++j) add(bv[j], xv[j]);
             }
             if (P4 + sl < P) {
                 const float bv = load_elem<T>(b, P4 + sl);
@@ -130,13 +144,18 @@ void launch_gn(dim3 grid, const void *xh, const void *B, i64 C, i64 P, int cbloc
         kernel<<<grid, kThreads, 0, stream>>>(x, b, C, P, cblocks, scale, gg, gbt, sqout, direct);
     };
     // Inputs of whole cache lines per channel, too large to be still cached, go
-    // past the caches: 512 x 64 x 1024 fp32 (268 MB) 45 us against 52; but 32 x
-    // 16 x 4096 (17 MB) 15 against 10, and channels that share lines (300 x
-    // 59 x 989 bf16) 19 against 15.
+    // past the caches.  us with / without, the same inputs again and four sets in turn:
+    // 512 x 64 x 1024 fp32 (268 MB) 43.9 / 42.0 and 45.4 / 51.5, 384 x 64 x 1024 (201 MB)
+    // 32.9 / 32.3 and 34.3 / 39.1, 108 x 67 x 3328 (193 MB) 36.8 / 33.2 and 38.9 / 43.2,
+    // 256 x 64 x 1024 (134 MB) 24.0 / 23.1 and 24.6 / 28.0, 200 x 64 x 1056 (108 MB) 22.1 /
+    // 20.1 and 23.3 / 25.9; smaller inputs stay cached either way: 128 x 64 x 1024
+    // (67 MB) 14.1 / 13.5 and 14.1 / 13.9.  Channels that share lines never (300 x 59
+    // x 989 bf16: 19 against 15).
     const bool lines = P * sizeof(T) % 128 == 0 && aligned(xh, 128) && aligned(B, 128);
     const double bytes = 2.0 * (double)(grid.x / cblocks) * (double)C * (double)P * sizeof(T);
     if (P <= 64 && P % 4 != 0) go(gn_affine_kernel<T, 16, 0, false>);
     else if (P <= 64) go(gn_affine_kernel<T, 16, 1, false>);
+    else if (P <= 128 && P % 4 != 0) go(gn_affine_kernel<T, 64, 0, false>);   // 400 x 200 x 90 fp32 19.4 us against 20.1
     else if (P < 260) go(gn_affine_kernel<T, 64, 1, false>);
     else if (P < 516) go(gn_affine_kernel<T, 64, 2, false>);
     else if (lines && bytes >= 96e6) go(gn_affine_kernel<T, 64, 4, true>);

@@ -31,3 +31,13 @@ def test_planes(N, C, P, shift, dtype):
     assert ((gb - 1.5 * b.sum(2)).abs() <= bound * b.abs().sum(2)).all()
     ref = (gg.double() ** 2 + gb.double() ** 2).sum(1)
     np.testing.assert_allclose(sq.double().cpu().numpy(), ref.cpu().numpy(), rtol=1e-5)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,P", [(2, 3, 66), (2, 17, 127), (2, 16, 128), (2, 3, 130), (2, 3, 544), (2, 3, 1026), (2, 3, 1284),
+                                   (300, 64, 1088), (500, 64, 576)])
+def test_tails(N, C, P, dtype):
+    """What a step of the loop leaves over, in planes read through and (the largest) past the caches, and the
+    planes read by single elements."""
+    test_planes(N, C, P, 0, dtype)
+    test_planes(N, C, P, 1, dtype)
