@@ -41,7 +41,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}     # dense MFMA peaks
+# dense MFMA peaks; bf16x3: fp32 operands as three bf16 parts, six bf16 products each
+PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "bf16x3": 2500.0 / 6}
 # fp32 vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2 (packed FP32) x 2.4 GHz
 ALU_PEAK_TFLOPS = 157.3
 METRIC = "DP-SGD grad step samples/sec at 1 MI355X; achieved HBM GB/s / MFMA util"
@@ -54,6 +55,28 @@ def log(*a):
 # ---------------------------------------------------------------------------
 # algorithmic cost of each call of the step
 # ---------------------------------------------------------------------------
+
+def conv_on_bf16_units(st, lb):
+    """Whether a Conv2d layer's automatic choice is the bf16-matrix kernel: its sums' order shows
+    against the fp32 row-chunked or tiled kernel on the same operands."""
+    import torch
+    from paper_2109_12298_amd import binding as dp
+    L, N = lb.layer, st.N
+    ho, wo = L.out_hw
+    geom = (L.k[0], L.k[1], L.stride[0], L.stride[1], L.pad[0], L.pad[1])
+    ws = torch.empty(max(dp.dp_grad_sample_conv2d_workspace_bytes(N, L.c_in, L.h, L.w, L.c_out, *geom), 4),
+                     dtype=torch.uint8, device=lb.A.device)
+    got = []
+    for path in (dp.DP_CONV_AUTO, dp.DP_CONV_ROWS):
+        gW = torch.empty(N, L.c_out, L.c_in * L.k[0] * L.k[1], device=lb.A.device)
+        before = dp.dp_conv2d_set_path(path)
+        dp.dp_grad_sample_conv2d(lb.A, lb.B, st.dt, N, L.c_in, L.h, L.w, L.c_out, ho, wo, *geom, 1, 1, 1, 1.0, gW, None,
+                                 None, None, ws)
+        dp.dp_conv2d_set_path(before)
+        got.append(gW)
+    torch.cuda.synchronize()
+    return not torch.equal(*got)
+
 
 def call_costs(st, nnz=None):
     """name -> (algorithmic bytes, flops, kernel name, MFMA peak key or None) per call of one step.
@@ -93,7 +116,7 @@ def call_costs(st, nnz=None):
                                          "bf16_grad_sample_kernel" if staged else
                                          "bf16_per_sample_kernel" if bf_mfma else
                                          "ps_split_kernel" if split else "ps_gemm_kernel",
-                                         "bf16" if bf_mfma else "f32")
+                                         "bf16" if bf_mfma or (bf and split) else "bf16x3" if split else "f32")
             if lb.clip_mode == "fused":
                 # all fused Linear layers' weight sums share one grouped call; their
                 # bias sums are column reductions of the stored bias gradients
@@ -113,12 +136,12 @@ def call_costs(st, nnz=None):
             grads = N * L.n_params * 4
             choice = dp.dp_conv2d_kernel_choice(N, L.c_in, L.h, L.w, L.c_out, L.k[0], L.k[1], L.stride[0],
                                                 L.stride[1], L.pad[0], L.pad[1])
-            kname = {dp.DP_CONV_KERNEL_SMALL: "conv_small_kernel",
-                     # (the row chunks run on either matrix unit, by the layer's sizes)
-                     dp.DP_CONV_KERNEL_ROWS: "conv_rows_kernel+conv_split_kernel"}.get(choice,
-                                                                                       "conv_per_sample_kernel")
+            kname, unit = {dp.DP_CONV_KERNEL_SMALL: "conv_small_kernel",
+                           dp.DP_CONV_KERNEL_ROWS: "conv_rows_kernel"}.get(choice, "conv_per_sample_kernel"), "f32"
+            if choice != dp.DP_CONV_KERNEL_SMALL and conv_on_bf16_units(st, lb):
+                kname, unit = "conv_split_kernel", "bf16" if bf else "bf16x3"
             out["grad:" + L.name] = (N * (L.c_in * L.h * L.w + L.c_out * ho * wo) * e + grads + N * 4,
-                                     2 * N * L.c_out * kk * ho * wo, kname, "f32")
+                                     2 * N * L.c_out * kk * ho * wo, kname, unit)
             col_bytes += grads
         elif isinstance(L, W.Embedding):
             u = (nnz or {}).get(L.name, N * L.T)
@@ -156,7 +179,7 @@ def call_costs(st, nnz=None):
             kinds.add({"bf16_grad_sample_kernel": "bf16_grad_group_kernel",
                        "ps_split_kernel": "ps_split_group_kernel"}.get(kn, "grad_many_kernel"))
         kname = "+".join(sorted(kinds))
-        mt = "bf16" if "bf16_grad_group_kernel" in kinds else "f32" if "ps_split_group_kernel" in kinds else None
+        mt = ("bf16" if "bf16_grad_group_kernel" in kinds else "bf16x3" if "ps_split_group_kernel" in kinds else None)
         out["grad:group"] = (gb_, gf_, kname, mt)
     if not st.fold_norms:
         out["norms"] = (len(st.layers) * N * 4 + N * 4, len(st.layers) * N, "norms_kernel", None)
