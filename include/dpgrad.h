@@ -486,7 +486,8 @@ dp_status dp_clip_accumulate_linear_many(const dp_linear_clip *items, int32_t co
  * at index cap or beyond are left out and set DP_FLAG_CAP; stored ids outside
  * [0, V) set DP_FLAG_BAD_INDEX and are left out.  Needs 64 * V < 2^31 and
  * cap < 2^31 (else DP_EUNSUPPORTED).  The workspace (16-byte aligned) holds
- * an inverted index of 64 samples at a time. */
+ * an inverted index of 64 samples at a time; it is required, but not used, where V <= 65536 and
+ * cap <= 256 N, as the stored ids are then scanned instead. */
 size_t dp_clip_accumulate_embedding_workspace_bytes(int64_t N, int64_t V);
 dp_status dp_clip_accumulate_embedding(const int64_t *row_ptr, const int64_t *uniq_ids,
                                        const float *rows, int64_t cap, const float *norm, float C,

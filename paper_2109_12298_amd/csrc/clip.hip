@@ -388,10 +388,13 @@ __global__ __launch_bounds__(kScanThreads) void emb_clipsum_scan_kernel(
 }
 
 // Every workgroup reads every stored id, so the scan pays while they are few
-// (up to 256 rows per sample, which cap bounds) and one workgroup per CU holds
-// the index of all ids.  64 samples with 256 distinct ids each: V = 10000 12.9
-// (index) against 9.8 us, V = 50000 22.4 against 16.6; with 512 each, V =
-// 10000: 12.7 against 14.5.
+// and one workgroup per CU holds the index of all ids.  cap bounds the stored
+// rows; how many there are is known on the device only.  64 samples of so many
+// distinct ids each, us scan / index: V = 10000 256 10.0 / 12.9, 384 12.3 / 12.9, 512
+// 14.7 / 13.0; V = 50000 256 18.0 / 23.0, 384 20.6 / 24.6, 512 22.4 / 25.6; 256 samples, V =
+// 10000 256 35.6 / 47.4, 512 49.3 / 52.3, 1024 74.9 / 62.7.  The line is where the scan is ahead by a
+// fifth with every id distinct; texts, which repeat ids, are ahead beyond it too
+// (T = 512 of Zipf ids, 166 of them stored: 11.6 / 13.8).
 bool emb_scan_ok(i64 N, i64 V, i64 cap)
 {
     return V <= kScanGroups * kScanIds && cap <= 256 * N;

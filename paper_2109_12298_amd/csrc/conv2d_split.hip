@@ -27,9 +27,9 @@
 // 19.3 GFLOP of bf16 MFMA, 62 us of it at the clock it runs at) a workgroup of
 // 44 us spends 2 on its start, 31 on its chunks (staging and multiplying by
 // turns, against the CU's other workgroup), 8 on its stores, which all
-// workgroups of a round issue at about the same time.  160 us against 223 on
-// fp32 MFMA (0.8e-7 against 1.9e-7 off 64 bits); 32 -> 64 @32^2 130 against
-// 192.  Tried: nine taps per wave with one accumulator each (faster staging
+// workgroups of a round issue at about the same time.  162 us against 223 on
+// fp32 MFMA; off 64 bits by 0.68e-7 (weights) and 0.84e-7 (bias) against 1.92e-7
+// and 1.51e-7; 32 -> 64 @32^2 130 against 192.  Tried: nine taps per wave with one accumulator each (faster staging
 // rounds, but 2.2e-7 off), six waves of one tap column (only one such
 // workgroup fits a CU), 16-byte instead of 4-byte stores of the outputs,
 // workgroups of a CU started apart or at different wave priorities (no change).

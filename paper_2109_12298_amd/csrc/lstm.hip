@@ -33,7 +33,7 @@
 // instructions cost (about 150 at H = 100, 104 of them multiply-adds) as long
 // as no SIMD has more than two; of the 0.6 us of a step at H = 100 another 0.25
 // are its chain (LDS write, barrier, LDS read, the permutes), which is all that
-// is left at H = 14.  64 samples, T = 256, H = 100: 159 us, against 184 with four lanes per
+// is left at H = 14.  64 samples, T = 256, H = 100: 160 us, against 184 with four lanes per
 // unit, where every wave read all of delta for a quarter as many
 // multiply-adds; 32 samples, T = 100, H = 120 73 / 93; 300 samples, T = 128,
 // H = 80 88 / 198; 512 samples, T = 64, H = 100 89 / 109; 16 samples, T = 100,

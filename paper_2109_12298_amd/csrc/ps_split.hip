@@ -6,7 +6,7 @@
 // fp32 results); bf16 operands go in as they are.
 //
 // Block = (sample, tile of gW_n).  Stages of consecutive positions are loaded
-// into registers two stages ahead, R rows x 16 bytes per thread, then split
+// into registers one or two stages ahead, R rows x 16 bytes per thread, then split
 // and written to LDS with the positions contiguous ([feature][t], one plane
 // per part; packing two positions of a feature into a word costs the same as
 // packing two features), so that an MFMA operand (eight positions of one
@@ -16,13 +16,12 @@
 // 43 MB and, in six products, 7.9 GFLOP of bf16 MFMA) about half of the call
 // is fixed (two launches, the first loads, the last stores) and a stage costs
 // its MFMAs plus about half of its split (the conversions and LDS writes
-// that the interleaving does not hide).  19.9-21.2 us against 24.3 with fp32
-// MFMA, and half the error against 64 bits (1.1e-7 against 2.1e-7); a bf16
-// layer of odd sizes (48 samples, T = 75, 300 -> 514, 36 MB) 20.2 us against
-// 42.0 with element loads and fp32 MFMA; 768 x 768 over T = 512 (16 samples,
-// fp32) 69.6 against 85.4; 38 samples, T = 23, 1419 -> 29 11.2 against 11.8.
-// Outputs written straight from the accumulators instead of by whole rows
-// through LDS took 21.4 and 25.1 us at the first two.
+// that the interleaving does not hide).  20.5-21.7 us against 24.3 with fp32
+// MFMA; off 64 bits by 0.90e-7 (weights) and 0.88e-7 (bias) against 2.05e-7 and
+// 1.00e-7.  A bf16 layer of odd sizes (48 samples, T = 75, 300 -> 514, 36 MB) 20.6 us
+// against 42.0 with element loads and fp32 MFMA; 768 x 768 over T = 512 (32 samples,
+// fp32) 131 against 164.  Outputs written straight from the accumulators
+// instead of by whole rows through LDS took 21.4 and 25.1 us at the first two.
 #include "common.hpp"
 #include "bf16_stage.hpp"
 #include "split_bf16.hpp"
