@@ -173,11 +173,11 @@ inline double cost_of(const SplitShape &s, const Layout &w, int64_t N, bool bf16
 
 // A plan's time in us, for comparison with the kernels it may replace; rounds:
 // of its grid over the CUs (cu_rounds), per CU: workgroups one after the other.
-// Fitted to 3300 drawn layers (the largest stay within 1.3 times, 8% rms for
-// fp32 and 14% for bf16): a fixed part, the stores (single words of every tap
-// per lane, each its own cache line, unless whole rows of 3 x 3 taps go through LDS), and per chunk the
-// round trips of its loads (two units per thread each), its units, and its
-// steps with their MFMAs.
+// Fitted to 3300 drawn layers (8% rms for fp32, 14% for bf16): a fixed part,
+// the stores (single words of every tap per lane, each its own cache line,
+// unless whole rows of 3 x 3 taps go through LDS), and per chunk the round trips
+// of its loads (two units per thread each), its units, and its steps with
+// their MFMAs.
 inline double split_us(const SplitShape &s, const Layout &w, bool bf16, double rounds, double per_cu)
 {
     const int chunks = (s.Ho + s.RC - 1) / s.RC, steps = ((s.RC * s.NU + 1) / 2 + w.wk - 1) / w.wk;
