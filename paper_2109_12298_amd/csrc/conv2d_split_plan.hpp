@@ -38,7 +38,8 @@ struct SplitShape {
     int inv_xrow, inv_grow;            // ceil(2^20 / (XR * NU)), ceil(2^20 / (RC * gl))
     int nci, nco, ngrp, gpw, tiles;    // channel tiles, groups, groups per workgroup, workgroups per sample
     int bias_at;                       // byte offset of the bias sums (one float per GY unit of a chunk), 0: none
-    bool full;                         // 3 x 3 taps in one group: stores by whole rows
+    int full;                          // 3 x 3 taps in one group: stores by whole rows (a bool costs registers:
+                                       // 100 samples 24 -> 40 @27^2 5 x 5 stride 2 bf16 36.1 us against 34.7)
     ConvGroup g[kMaxGroups];
 };
 
