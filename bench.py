@@ -56,9 +56,9 @@ def log(*a):
 # algorithmic cost of each call of the step
 # ---------------------------------------------------------------------------
 
-def conv_on_bf16_units(st, lb):
+def conv_on_bf16_units(st, lb, choice):
     """Whether a Conv2d layer's automatic choice is the bf16-matrix kernel: its sums' order shows
-    against the fp32 row-chunked or tiled kernel on the same operands."""
+    against the row-chunked or tiled kernel that would run in its place."""
     import torch
     from paper_2109_12298_amd import binding as dp
     L, N = lb.layer, st.N
@@ -67,7 +67,7 @@ def conv_on_bf16_units(st, lb):
     ws = torch.empty(max(dp.dp_grad_sample_conv2d_workspace_bytes(N, L.c_in, L.h, L.w, L.c_out, *geom), 4),
                      dtype=torch.uint8, device=lb.A.device)
     got = []
-    for path in (dp.DP_CONV_AUTO, dp.DP_CONV_ROWS):
+    for path in (dp.DP_CONV_AUTO, dp.DP_CONV_ROWS if choice == dp.DP_CONV_KERNEL_ROWS else dp.DP_CONV_TILED):
         gW = torch.empty(N, L.c_out, L.c_in * L.k[0] * L.k[1], device=lb.A.device)
         before = dp.dp_conv2d_set_path(path)
         dp.dp_grad_sample_conv2d(lb.A, lb.B, st.dt, N, L.c_in, L.h, L.w, L.c_out, ho, wo, *geom, 1, 1, 1, 1.0, gW, None,
@@ -138,7 +138,7 @@ def call_costs(st, nnz=None):
                                                 L.stride[1], L.pad[0], L.pad[1])
             kname, unit = {dp.DP_CONV_KERNEL_SMALL: "conv_small_kernel",
                            dp.DP_CONV_KERNEL_ROWS: "conv_rows_kernel"}.get(choice, "conv_per_sample_kernel"), "f32"
-            if choice != dp.DP_CONV_KERNEL_SMALL and conv_on_bf16_units(st, lb):
+            if choice != dp.DP_CONV_KERNEL_SMALL and conv_on_bf16_units(st, lb, choice):
                 kname, unit = "conv_split_kernel", "bf16" if bf else "bf16x3"
             out["grad:" + L.name] = (N * (L.c_in * L.h * L.w + L.c_out * ho * wo) * e + grads + N * 4,
                                      2 * N * L.c_out * kk * ho * wo, kname, unit)
