@@ -411,12 +411,8 @@ def cpu_baseline(wl, inputs, budget_s: float):
     from paper_2109_12298_amd import workloads as W
     N = wl.N
 
-    def sub(n):
-        return [W.LayerInputs(li.layer, A=None if li.A is None else li.A[:n], B=li.B[:n],
-                              ids=None if li.ids is None else li.ids[:n]) for li in inputs]
-
     def timed(n, step):
-        s_ = sub(n)
+        s_ = W.take_samples(inputs, slice(0, n))
         t0 = time.perf_counter()
         oracle.dp_step(wl, s_, step=step, denom=float(N))
         return time.perf_counter() - t0

@@ -353,3 +353,13 @@ def test_sequence_kernel_takes_no_more_positions_than_its_indexes_hold():
         assert ok(dt, 2, 8, 8) and ok(dt, 2 ** 30, 8, 8)
         taken = [T for T in list(range(top - 600, top + 1)) + [2 ** 31, 2 ** 40 - 1] if ok(dt, T, 8, 8)]
         assert all(T + 3 * 64 <= top for T in taken)
+
+
+def test_cpu_baseline_takes_samples_of_every_workload_s_inputs():
+    """Layers whose backprop the step derives (an LSTM's) come with none."""
+    import bench
+
+    wl = W.get("text_lstm_bptt")
+    small = W.Workload(0, wl.name, 2, wl.dtype, wl.C, wl.sigma, wl.layers)
+    got = bench.cpu_baseline(small, W.take_samples(W.make_inputs(wl), slice(0, 2)), 0.01)
+    assert got["value"] > 0 and got["single_thread"]["value"] > 0
